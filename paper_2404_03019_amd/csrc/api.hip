@@ -1213,6 +1213,7 @@ static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num
     const size_t o_key = transpose && !packed ? take((size_t)nnz * 8) : 0;
     const size_t o_row = transpose && !packed ? take((size_t)nnz * 8) : 0;
     const size_t o_w = transpose && !packed ? take((size_t)nnz * 4) : 0;
+    const size_t o_part = pull ? take(pull_part_bytes(nnz, F)) : 0;
     ScratchGuard sg;
     sg.st = st;
     geot_status_t s = scratch_alloc(&sg.p, at, st);
@@ -1255,8 +1256,8 @@ static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num
                                   bucket_b ? base + o_bucket : nullptr, pull, &rec_words, nullptr, st),
                  "launch transpose kernels");
         if (pull) {
-            GEOT_HIP(launch_gs_bwd_x_max_pull(rec, (const int64_t *)(base + o_off), arg, grad_out, nx, num_rows, F, V,
-                                              grad_X, st),
+            GEOT_HIP(launch_gs_bwd_x_max_pull(rec, (const int64_t *)(base + o_off), arg, grad_out, nnz, nx, num_rows, F, V,
+                                              (float *)(base + o_part), grad_X, st),
                      "launch max pull kernel");
             void *p_pull = sg.p;
             sg.p = nullptr;

@@ -878,125 +878,92 @@ __global__ __launch_bounds__(256) void gs_bwd_max_arg_run_kernel(const typename 
     flush();
 }
 
-// fused form, max, w.r.t. X, pulled over the transposed list: a row group per X row c walks the
-// records of column c (16-byte records {column, row, coefficient, edge}, sorted by column;
-// column starts in off) and sums coefficient * grad_out[row, f] over the features f whose
-// recipient is that edge. Every row of grad_X is written once: no fill and no float atomics
-// (on the SpMM graph 313 M of them, about 10 ms). Records load kU at a time.
-template <int V>
-__global__ __launch_bounds__(256) void gs_bwd_x_max_pull_kernel(const int32_t *__restrict__ rec,
+// fused form, max, w.r.t. X, pulled over the transposed list (16-byte records {column, row,
+// coefficient, edge}, sorted by column): grad_X[c, f] = the sum of coefficient * grad_out[row, f]
+// over the records of column c whose edge is the recipient of (row, f). Every row of grad_X is
+// written once: no fill and no float atomics (on the SpMM graph 313 M of them, about 10 ms).
+//
+// A row group takes a run of consecutive records, whatever their columns: bound by the recipient
+// rows each record gathers (and the latency of the grad_out rows behind them), it needs every
+// group to have the same work. A group per column left a column of 12,600 of 8,000,000 edges
+// (sources drawn with popularity, 400,000 columns of 64 features) to one group: 4.14 ms for the
+// pass, 0.47 ms by runs. Where the columns are even (the SpMM graph, uniform sources) both take
+// the same: 13.7 ms for the whole max forward and gradient. A column that lies in one
+// run is stored by it; one that continues into other runs leaves a partial sum per run (part[run]:
+// slot 0 for the run's first column, slot 1 for its last), which pull_join_kernel adds. Records
+// load kU at a time, grad_out rows only where the record's edge receives one of the thread's
+// features (the SpMM graph: 5.34 -> 4.53 ms; most records receive none).
+// Records per run: short ones where there are few groups, long ones where the partials of columns
+// that span runs cost more than the balance gives (whole gradient w.r.t. X, us at runs of 32 / 64 /
+// 128 / 256 / 512: 400,000 edges of 64 columns 131 / 136 / 158 / 204 / 298; 1,000,000 of 100: 295 /
+// 303 / 288 / 316 / 421; 8,000,000 of 64: 751 / 732 / 728 / 768 / 703; the SpMM graph 5,794 / 5,482
+// / 5,298 / 5,200 / 5,217).
+int pull_run(int64_t n) {
+    return n >= ((int64_t)1 << 24) ? 512 : n >= ((int64_t)1 << 20) ? 128 : 32;
+}
+
+template <int V, bool COOP>
+__global__ __launch_bounds__(256) void gs_bwd_x_max_pull_kernel(const int4 *__restrict__ rec,
                                                                 const int64_t *__restrict__ off,
                                                                 const unsigned *__restrict__ arg,
-                                                                const float *__restrict__ gout, int64_t nx, int64_t R,
-                                                                int64_t F, float *__restrict__ gX) {
+                                                                const float *__restrict__ gout, int run, int64_t nx,
+                                                                int64_t R, int64_t F, float *__restrict__ gX,
+                                                                float *__restrict__ part) {
     constexpr int kU = 4;
-    // the column's terms add into `run`, which joins acc every kPullRun records, so a hub
-    // column's long chain rounds like short runs (the fp32 bound holds)
-    constexpr int kPullRun = 256;
     const int nvec = (int)(F / V);
-    const RowMap m = row_map(nvec);
-    if (nvec <= m.tpr && m.tpr >= kU) {
-        // One vector per thread: the group loads up to tpr records of its column at once (lane i
-        // the i-th: one coalesced load instead of one broadcast load per record) and hands them
-        // out by lane shuffles, so a batch waits only for its recipients and grad_out rows. The
-        // batches are the same runs of kU records as below, so the sums are the same.
-        const int4 *rec4 = reinterpret_cast<const int4 *>(rec);
-        const int gb = (int)(threadIdx.x & 63) - m.j0;   // the group's first lane in the wave
-        const bool lane = m.j0 < nvec;
-        for (int q = 0; q < kPasses; ++q) {
-            const int64_t c = m.row(q);
-            if (c >= nx) break;   // the same for the whole group
-            const int64_t lo = off[c], hi = off[c + 1];
-            float acc[V], run[V];
+    const RowMap m = row_map(nvec, 1);
+    const int64_t q = (int64_t)blockIdx.x * m.rows + m.rsub;
+    const int64_t n = off[nx];   // records in the list: the edges whose column is in range
+    const int64_t lo = q * run, hi = min(lo + run, n);
+    if (lo >= n) return;   // the same for the whole group
+    const int gb = (int)(threadIdx.x & 63) - m.j0;   // the group's first lane in the wave
+    const int before = lo > 0 ? rec[lo - 1].x : -1, after = hi < n ? rec[hi].x : -1;
+    const int first = rec[lo].x;
+    for (int jt = 0; jt < nvec; jt += m.tpr) {   // one round unless a row has more than 64 vectors
+        const int j = jt + m.j0;
+        const bool lane = j < nvec;
+        float acc[V];
 #pragma unroll
-            for (int k = 0; k < V; ++k) acc[k] = run[k] = 0.0f;
-            int steps = 0;
-            for (int64_t k0 = lo; k0 < hi; k0 += m.tpr) {
-                const int4 mine = k0 + m.j0 < hi ? rec4[k0 + m.j0] : make_int4(0, -1, 0, 0);
-                const int cnt = (int)min((int64_t)m.tpr, hi - k0);
-                for (int u0 = 0; u0 < cnt; u0 += kU) {
-                    int r[kU];
-                    unsigned ed[kU];
-                    float coef[kU];
+        for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+        int cur = first;
+        // the sum of column `cur` over this run's records: grad_X where the column lies in the run
+        auto put = [&](bool last) {
+            if (!lane || (uint64_t)(int64_t)cur >= (uint64_t)nx) return;
+            const bool head = cur == first;
+            if ((head && cur == before) || (last && cur == after))
+                store_vec<V>(part + (2 * q + (head ? 0 : 1)) * F + (int64_t)j * V, acc);
+            else
+                store_vec<V>(gX + (int64_t)cur * F + (int64_t)j * V, acc);
+        };
+        // COOP: the group loads tpr records at once (lane i the i-th: one coalesced load instead of a
+        // broadcast load per record) and hands them out by lane shuffles
+        const int step = COOP ? m.tpr : kU;
+        for (int64_t k0 = lo; k0 < hi; k0 += step) {
+            int4 mine = make_int4(0, -1, 0, 0);
+            if (COOP && k0 + m.j0 < hi) mine = rec[k0 + m.j0];
+            const int cnt = (int)min((int64_t)step, hi - k0);
+            for (int u0 = 0; u0 < cnt; u0 += kU) {
+                int4 t[kU];   // COOP: rows and edges now, columns and coefficients where they are used
 #pragma unroll
-                    for (int u = 0; u < kU; ++u) {   // u0 + u < tpr: past the column, the sentinel
-                        const int src = gb + u0 + u;
-                        r[u] = __shfl(mine.y, src, 64);
-                        coef[u] = __int_as_float(__shfl(mine.z, src, 64));
-                        ed[u] = (unsigned)__shfl(mine.w, src, 64);
-                    }
-                    unsigned a[kU][V];
-                    float g[kU][V];
-#pragma unroll
-                    for (int u = 0; u < kU; ++u) {
-                        if (lane && (uint64_t)(int64_t)r[u] < (uint64_t)R) {
-                            load_arg<unsigned, V>(arg + (int64_t)r[u] * F + (int64_t)m.j0 * V, a[u]);
-                        } else {
-#pragma unroll
-                            for (int k = 0; k < V; ++k) a[u][k] = ~0u;
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < kU; ++u) {
-                        bool any = false;
-#pragma unroll
-                        for (int k = 0; k < V; ++k) any |= a[u][k] == ed[u];
-                        if (any) {
-                            load_f32<V>(gout + (int64_t)r[u] * F + (int64_t)m.j0 * V, g[u]);
-                        } else {
-#pragma unroll
-                            for (int k = 0; k < V; ++k) g[u][k] = 0.0f;
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < kU; ++u)
-#pragma unroll
-                        for (int k = 0; k < V; ++k)
-                            if (a[u][k] == ed[u]) run[k] += coef[u] * g[u][k];
-                    if (++steps == kPullRun / kU) {
-#pragma unroll
-                        for (int k = 0; k < V; ++k) {
-                            acc[k] += run[k];
-                            run[k] = 0.0f;
-                        }
-                        steps = 0;
+                for (int u = 0; u < kU; ++u) {   // past the run: a row out of range, and not reduced
+                    if constexpr (COOP) {
+                        t[u].y = __shfl(mine.y, gb + u0 + u, 64);
+                        t[u].w = __shfl(mine.w, gb + u0 + u, 64);
+                    } else {
+                        t[u] = k0 + u < hi ? rec[k0 + u] : make_int4(0, -1, 0, 0);
                     }
                 }
-            }
-#pragma unroll
-            for (int k = 0; k < V; ++k) acc[k] += run[k];
-            if (lane) store_vec<V>(gX + c * F + (int64_t)m.j0 * V, acc);
-        }
-        return;
-    }
-    for (int q = 0; q < kPasses; ++q) {
-        const int64_t c = m.row(q);
-        if (c >= nx) break;
-        const int64_t lo = off[c], hi = off[c + 1];
-        for (int j = m.j0; j < nvec; j += m.tpr) {
-            float acc[V], run[V];
-#pragma unroll
-            for (int k = 0; k < V; ++k) acc[k] = run[k] = 0.0f;
-            int steps = 0;
-            for (int64_t k0 = lo; k0 < hi; k0 += kU) {
-                int4 t[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u)
-                    t[u] = k0 + u < hi ? *reinterpret_cast<const int4 *>(rec + 4 * (k0 + u)) : make_int4(0, -1, 0, 0);
-                float g[kU][V];
                 unsigned a[kU][V];
+                float g[kU][V];
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
-                    const int64_t r = (int64_t)t[u].y;
-                    if ((uint64_t)r < (uint64_t)R) {
-                        load_arg<unsigned, V>(arg + r * F + (int64_t)j * V, a[u]);
+                    if (lane && (uint64_t)(int64_t)t[u].y < (uint64_t)R) {
+                        load_arg<unsigned, V>(arg + (int64_t)t[u].y * F + (int64_t)j * V, a[u]);
                     } else {
 #pragma unroll
                         for (int k = 0; k < V; ++k) a[u][k] = ~0u;
                     }
                 }
-                // grad_out only where the record's edge receives one of this thread's features
-                // (the SpMM graph: 5.34 -> 4.53 ms; most records receive none)
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
                     bool any = false;
@@ -1011,23 +978,116 @@ __global__ __launch_bounds__(256) void gs_bwd_x_max_pull_kernel(const int32_t *_
                 }
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
+                    if (u0 + u >= cnt) break;
+                    if constexpr (COOP) {
+                        t[u].x = __shfl(mine.x, gb + u0 + u, 64);
+                        t[u].z = __shfl(mine.z, gb + u0 + u, 64);
+                    }
+                    if (t[u].x != cur) {
+                        put(false);
+                        cur = t[u].x;
+#pragma unroll
+                        for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+                    }
                     const float coef = __int_as_float(t[u].z);
 #pragma unroll
                     for (int k = 0; k < V; ++k)
-                        if (a[u][k] == (unsigned)t[u].w) run[k] += coef * g[u][k];
+                        if (a[u][k] == (unsigned)t[u].w) acc[k] += coef * g[u][k];
                 }
-                if (++steps == kPullRun / kU) {
+            }
+        }
+        put(true);
+    }
+}
+
+// grad_X of the columns the pull's runs leave: a column without records is zero, one that spans
+// runs is the sum of its runs' partials. A block takes 256 columns, one per thread to look at, and
+// its row groups write those that need it (a group per column looked at 8 columns per block: 34
+// us for 400,000 columns; 14 us so). A column of more than kJoinMine runs is left to the whole block,
+// its groups taking every m.rows-th partial each.
+constexpr int kJoinMine = 32;
+
+template <int V>
+__global__ __launch_bounds__(256) void pull_join_kernel(const int64_t *__restrict__ off, int run, int64_t nx, int64_t F,
+                                                        const float *__restrict__ part, float *__restrict__ gX) {
+    constexpr int kU = 4;
+    __shared__ int s_n, s_nlong;
+    __shared__ int64_t s_lo[256], s_hi[256];
+    __shared__ uint8_t s_col[256], s_long[256];   // the block's columns to write, by groups and by the block
+    __shared__ float s_v[256 * V];
+    const int nvec = (int)(F / V);
+    const RowMap m = row_map(nvec, 1);
+    if (threadIdx.x == 0) s_n = s_nlong = 0;
+    __syncthreads();
+    const int64_t c0 = (int64_t)blockIdx.x * 256;
+    if (c0 + threadIdx.x < nx) {
+        const int64_t lo = off[c0 + threadIdx.x], hi = off[c0 + threadIdx.x + 1];
+        const int64_t runs = hi > lo ? (hi - 1) / run - lo / run + 1 : 0;   // 1: written by its run
+        s_lo[threadIdx.x] = lo;
+        s_hi[threadIdx.x] = hi;
+        if (runs > kJoinMine) s_long[atomicAdd(&s_nlong, 1)] = (uint8_t)threadIdx.x;
+        else if (runs != 1) s_col[atomicAdd(&s_n, 1)] = (uint8_t)threadIdx.x;
+    }
+    __syncthreads();
+    // the partial of run q of a column that starts at record `lo` and run q0
+    auto slot = [&](int64_t q, int64_t q0, int64_t lo) {
+        return part + (2 * q + (q == q0 && lo != q0 * run ? 1 : 0)) * F;
+    };
+    auto add = [&](float *acc, int64_t q, int64_t q1, int64_t by, int64_t q0, int64_t lo, int j) {
+        for (; q <= q1; q += kU * by) {
+            float x[kU][V];
 #pragma unroll
-                    for (int k = 0; k < V; ++k) {
-                        acc[k] += run[k];
-                        run[k] = 0.0f;
-                    }
-                    steps = 0;
+            for (int u = 0; u < kU; ++u) {
+                if (q + u * by <= q1) {
+                    load_f32<V>(slot(q + u * by, q0, lo) + (int64_t)j * V, x[u]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < V; ++k) x[u][k] = 0.0f;
                 }
             }
 #pragma unroll
-            for (int k = 0; k < V; ++k) acc[k] += run[k];
-            store_vec<V>(gX + c * F + (int64_t)j * V, acc);
+            for (int k = 0; k < V; ++k) acc[k] += (x[0][k] + x[1][k]) + (x[2][k] + x[3][k]);
+        }
+    };
+    for (int i = m.rsub; i < s_n; i += m.rows) {
+        const int t = s_col[i];
+        const int64_t lo = s_lo[t], hi = s_hi[t];
+        const int64_t q0 = lo / run, q1 = (hi - 1) / run;
+        for (int j = m.j0; j < nvec; j += m.tpr) {
+            float acc[V];
+#pragma unroll
+            for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+            if (hi > lo) add(acc, q0, q1, 1, q0, lo, j);
+            store_vec<V>(gX + (c0 + t) * F + (int64_t)j * V, acc);
+        }
+    }
+    const int nlong = s_nlong;
+    for (int i = 0; i < nlong; ++i) {
+        const int t = s_long[i];
+        const int64_t lo = s_lo[t], hi = s_hi[t];
+        const int64_t q0 = lo / run, q1 = (hi - 1) / run;
+        for (int jt = 0; jt < nvec; jt += m.tpr) {
+            const int j = jt + m.j0;
+            float acc[V];
+#pragma unroll
+            for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+            if (j < nvec) add(acc, q0 + m.rsub, q1, m.rows, q0, lo, j);
+#pragma unroll
+            for (int k = 0; k < V; ++k) s_v[threadIdx.x * V + k] = acc[k];
+            __syncthreads();
+            for (int h = m.rows >> 1; h > 0; h >>= 1) {   // the groups' sums, pairwise
+                if (m.rsub < h) {
+#pragma unroll
+                    for (int k = 0; k < V; ++k) s_v[threadIdx.x * V + k] += s_v[(threadIdx.x + h * m.tpr) * V + k];
+                }
+                __syncthreads();
+            }
+            if (m.rsub == 0 && j < nvec) {
+#pragma unroll
+                for (int k = 0; k < V; ++k) acc[k] = s_v[threadIdx.x * V + k];
+                store_vec<V>(gX + (c0 + t) * F + (int64_t)j * V, acc);
+            }
+            __syncthreads();
         }
     }
 }
@@ -1438,11 +1498,13 @@ __global__ __launch_bounds__(256) void scan_sums_kernel(int64_t *sums, int64_t n
     }
 }
 
-__global__ __launch_bounds__(256) void scan_add_kernel(int64_t *off, int64_t n, const int64_t *sums,
-                                                       int64_t total_slot) {
+__global__ __launch_bounds__(256) void scan_add_kernel(const unsigned *counts, int64_t *off, int64_t n,
+                                                       const int64_t *sums) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) off[i] += sums[i / kScanTile];
-    if (i == 0) off[n] = total_slot;
+    if (i >= n) return;
+    const int64_t o = off[i] + sums[i / kScanTile];
+    off[i] = o;
+    if (i == n - 1) off[n] = o + (int64_t)counts[i];
 }
 
 // edge e goes to slot off[col[e]] + (a decrementing per-row cursor): the
@@ -1989,9 +2051,8 @@ int64_t grid_rows(int64_t rows, int nvec, int passes = kPasses) {
     return b < 1 ? 1 : b;
 }
 
-// exclusive scan of len unsigned counts into off (sums: ceil(len / kScanTile) scratch); off[len] = last
-hipError_t scan_counts(const unsigned *counts, int64_t len, int64_t *off, int64_t *sums, int64_t last,
-                       hipStream_t st) {
+// exclusive scan of len unsigned counts into off (sums: ceil(len / kScanTile) scratch); off[len] = their sum
+hipError_t scan_counts(const unsigned *counts, int64_t len, int64_t *off, int64_t *sums, hipStream_t st) {
     const int64_t ntiles = (len + kScanTile - 1) / kScanTile;
     if (ntiles > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)ntiles), dim3(256), 0, st, counts, len, off, sums);
@@ -1999,7 +2060,7 @@ hipError_t scan_counts(const unsigned *counts, int64_t len, int64_t *off, int64_
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, st, sums, ntiles);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, off, len, sums, last);
+    hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, counts, off, len, sums);
     return hipGetLastError();
 }
 
@@ -2145,7 +2206,7 @@ hipError_t launch_transpose_t(const I *col, int64_t nx, const I *row, const floa
     const unsigned ge = (unsigned)geb;
     hipLaunchKernelGGL(hist_kernel<I>, dim3(ge), dim3(256), 0, st, col, n, nx, counts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = scan_counts(counts, nx, off, sums, n, st)) != hipSuccess) return e;
+    if ((e = scan_counts(counts, nx, off, sums, st)) != hipSuccess) return e;
     if (rec)
         hipLaunchKernelGGL((place_kernel<true, I>), dim3(ge), dim3(256), 0, st, col, nx, row, w, roff, nrows,
                            mean ? 1 : 0, n,
@@ -2175,23 +2236,37 @@ hipError_t launch_transpose(const void *col, int64_t nx, const void *row, int id
                               arrays_written, st);
 }
 
-hipError_t launch_gs_bwd_x_max_pull(const int32_t *rec, const int64_t *off, const void *arg, const float *gout,
-                                    int64_t nx, int64_t R, int64_t F, int V, float *gX, hipStream_t st) {
-    if (nx <= 0 || F <= 0) return hipSuccess;
-    if (!(V == 1 || V == 2 || V == 4 || V == 8) || F % V != 0) return hipErrorInvalidValue;
-    const int64_t gb = grid_rows(nx, (int)(F / V));
-    if (gb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const unsigned g = (unsigned)gb;
+size_t pull_part_bytes(int64_t n, int64_t F) {
+    const int run = pull_run(n);
+    return (size_t)((n + run - 1) / run) * 2 * (size_t)F * 4;
+}
+
+hipError_t launch_gs_bwd_x_max_pull(const int32_t *rec, const int64_t *off, const void *arg, const float *gout, int64_t n,
+                                    int64_t nx, int64_t R, int64_t F, int V, float *part, float *gX, hipStream_t st) {
+    if (nx <= 0 || F <= 0 || n <= 0) return hipSuccess;
+    if (!(V == 1 || V == 2 || V == 4) || F % V != 0) return hipErrorInvalidValue;
+    const int nvec = (int)(F / V);
+    const int run = pull_run(n);
+    const int64_t gp = grid_rows((n + run - 1) / run, nvec, 1), gj = (nx + 255) / 256;
+    if (gp > 0x7fffffffLL || gj > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const int4 *r = reinterpret_cast<const int4 *>(rec);
     const unsigned *a = static_cast<const unsigned *>(arg);
-    if (V == 8)
-        hipLaunchKernelGGL(gs_bwd_x_max_pull_kernel<8>, dim3(g), dim3(256), 0, st, rec, off, a, gout, nx, R, F, gX);
-    else if (V == 4)
-        hipLaunchKernelGGL(gs_bwd_x_max_pull_kernel<4>, dim3(g), dim3(256), 0, st, rec, off, a, gout, nx, R, F, gX);
-    else if (V == 2)
-        hipLaunchKernelGGL(gs_bwd_x_max_pull_kernel<2>, dim3(g), dim3(256), 0, st, rec, off, a, gout, nx, R, F, gX);
-    else
-        hipLaunchKernelGGL(gs_bwd_x_max_pull_kernel<1>, dim3(g), dim3(256), 0, st, rec, off, a, gout, nx, R, F, gX);
-    return hipGetLastError();
+    auto go = [&](auto vt) -> hipError_t {
+        constexpr int VV = decltype(vt)::value;
+        if (row_threads(nvec) >= 4)
+            hipLaunchKernelGGL((gs_bwd_x_max_pull_kernel<VV, true>), dim3((unsigned)gp), dim3(256), 0, st, r, off, a,
+                               gout, run, nx, R, F, gX, part);
+        else
+            hipLaunchKernelGGL((gs_bwd_x_max_pull_kernel<VV, false>), dim3((unsigned)gp), dim3(256), 0, st, r, off, a,
+                               gout, run, nx, R, F, gX, part);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(pull_join_kernel<VV>, dim3((unsigned)gj), dim3(256), 0, st, off, run, nx, F, part, gX);
+        return hipGetLastError();
+    };
+    if (V == 4) return go(std::integral_constant<int, 4>{});
+    if (V == 2) return go(std::integral_constant<int, 2>{});
+    return go(std::integral_constant<int, 1>{});
 }
 
 hipError_t launch_unpack(const int32_t *rec, int64_t n, int64_t *key_t, int64_t *row_t, float *w_t,

@@ -1,0 +1,73 @@
+"""The max gradient w.r.t. X over the transposed list, which is walked in runs of equally many
+records: columns of one record, columns that end at a run's edge, span two runs or hundreds, columns
+without records, and edges whose column is out of range. Against the oracle within the sum bound."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2404_03019_amd as geot
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def up(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def columns(kind, n, nx, rng):
+    if kind == "one":            # a single column over every run
+        return np.full(n, nx // 2)
+    if kind == "runs":           # columns of 32, 64, 31, 33, 1, 128, ... edges: ends at and beside run edges
+        lens = np.resize([32, 64, 31, 33, 1, 128, 96, 2, 30], n)
+        return np.repeat(np.arange(n), lens)[:n] % nx
+    if kind == "hub":            # half of the edges in one column, most others empty
+        return np.where(rng.random(n) < 0.5, 3, rng.integers(0, nx, n) // 50 * 50 % nx)
+    return rng.integers(0, nx, n)
+
+
+@pytest.mark.parametrize("F", [1, 3, 8, 47, 64, 260])
+@pytest.mark.parametrize("kind,n,nx", [("one", 1, 5), ("one", 33, 5), ("one", 2500, 7), ("runs", 3000, 700),
+                                       ("hub", 4111, 900), ("even", 2048, 257), ("even", 95, 4000)])
+def test_pull_runs(kind, n, nx, F):
+    rng = np.random.default_rng(n + F)
+    R = max(1, n // 6)
+    row = np.sort(rng.integers(0, R, n)).astype(np.int64)
+    col = columns(kind, n, nx, rng).astype(np.int64)
+    rng.shuffle(col)
+    X = rng.standard_normal((nx, F), dtype=np.float32)
+    w = rng.random(n, dtype=np.float32)
+    g = rng.standard_normal((R, F), dtype=np.float32)
+    say(f"pull {kind} n={n} nx={nx} F={F}")
+    ref_out = oracle.gather_scatter(X, col, w, row, R, "max")
+    rx, _ = oracle.gather_scatter_backward(X, col, w, row, g, "max", ref_out)
+    tx, _ = oracle.gather_scatter_backward(X, col, w, row, g, "max", ref_out, absolute=True)
+    out, arg = geot.gather_scatter_max_arg(up(X), up(col), up(w), up(row), R)
+    gx, _ = geot.gather_scatter_backward_max_arg(up(X), up(col), up(w), up(row), up(g), arg, need_weight=False)
+    err = np.abs(gx.cpu().numpy().astype(np.float64) - rx)
+    assert np.all(err <= 1e-5 * tx + 1e-6)
+
+
+@pytest.mark.parametrize("n", [3000, (1 << 20) + 77])   # the direct and the radix transposition
+def test_pull_skips_columns_out_of_range(n):
+    """Edges without a source take no part: the gradient equals the one of the list without them."""
+    rng = np.random.default_rng(n)
+    R, nx, F = n // 5, 4096, 8
+    row = np.sort(rng.integers(0, R, n)).astype(np.int64)
+    col = rng.integers(0, nx, n).astype(np.int64)
+    bad = rng.random(n) < 0.1
+    X = rng.integers(-8, 9, (nx, F)).astype(np.float32)
+    g = rng.integers(-4, 5, (R, F)).astype(np.float32)     # sums of integers: exact in any order
+    say(f"pull, columns out of range, n={n}")
+    keep = ~bad
+    _, arg = geot.gather_scatter_max_arg(up(X), up(col[keep]), None, up(row[keep]), R)
+    want, _ = geot.gather_scatter_backward_max_arg(up(X), up(col[keep]), None, up(row[keep]), up(g), arg)
+    edge = np.flatnonzero(keep).astype(np.int64)           # the same recipients by the whole list's numbers
+    a = arg.cpu().numpy().view(np.uint32).astype(np.int64)
+    a = np.where(a == 0xFFFFFFFF, 0xFFFFFFFF, edge[np.minimum(a, edge.size - 1)]).astype(np.uint32).view(np.int32)
+    wrong = col.copy()
+    wrong[bad] = rng.choice([-1, nx, nx + 5, -(1 << 40)], int(bad.sum()))
+    got, _ = geot.gather_scatter_backward_max_arg(up(X), up(wrong), None, up(row), up(g), up(a))
+    assert torch.equal(got, want)

@@ -545,16 +545,11 @@ int64_t piece_rows_k(int64_t n, int64_t G) {
     return std::max<int64_t>(1, std::min<int64_t>(8, ceil_div(n, G)));
 }
 
-// blocks that write the gap list, as a pass of their own or riding on the final partial level
+// blocks that write the gap list, as a pass of their own or riding on the final partial level (or join)
 constexpr int kFoldedGapBlocks = 1024;
 // segment sum and max gradients from this many bytes of grad_src take the offsets pass first
 // (below, the kernels read the ids, which saves two launches)
 constexpr size_t kBcastOffsetsMinBytes = (size_t)64 << 20;
-
-geot_status_t run_ep_levels(const Problem &p, const Resolved &r, const std::vector<Level> &lv,
-                            char *base, const std::vector<size_t> &off_v,
-                            const std::vector<size_t> &off_s, const std::vector<size_t> &off_c,
-                            const std::vector<size_t> &off_x, int64_t ld_p, GapList gaps, hipStream_t st);
 
 // Shape of the passes over fp32 partials: 8-element vectors (16-bit storage)
 // become 4-element vectors over twice the lanes, so the column tiles match.
@@ -571,7 +566,16 @@ struct EpPlan {
     std::vector<size_t> off_v, off_s, off_c, off_x;  // per level: values, segment ids, counts, recipients
     size_t bytes = 0;
     int64_t ld_p = 0;
+    bool join = false;   // the partials are joined in one launch (lv[1] is their list), not by levels
 };
+
+// Joining the partials directly is one launch for the two or three of the levels (2,000,000 rows of
+// 16 columns: 36 against 43 us for the call, of 64: 100 against 109, 65,536 of 32: 12 against 15).
+// But one block reads all partials of the longest segment, at about 80 GB/s: with half (all but
+// 5 %) of the 2,000,000 rows of 64 columns in one segment 112 (118) against 107 (105) us. So it takes lists
+// up to kJoinBytes, where segments average at most kJoinSpan blocks' rows; a list twice as long
+// costs less than 4 % of its call by levels.
+constexpr int64_t kJoinChunks = 16384, kJoinBytes = (int64_t)2 << 20, kJoinSpan = 4;
 
 geot_status_t plan_ep(const Problem &p, const Resolved &r, EpPlan *pl) {
     const int64_t G = kBlock / r.L;
@@ -582,7 +586,11 @@ geot_status_t plan_ep(const Problem &p, const Resolved &r, EpPlan *pl) {
     std::vector<Level> &lv = pl->lv;
     lv.clear();
     lv.push_back({p.nnz, r.K, ceil_div(p.nnz, G * r.K)});
-    while (lv.back().nchunks > 1) {
+    const int64_t chunks = lv[0].nchunks;
+    pl->join = chunks > 1 && chunks <= kJoinChunks && p.F <= kJoinBytes / 4 / chunks &&
+               p.nnz <= p.S * (G * r.K * kJoinSpan);
+    if (pl->join) lv.push_back({2 * chunks, 0, 0});
+    while (!pl->join && lv.back().nchunks > 1) {
         const int64_t n = 2 * lv.back().nchunks;
         const int64_t K = piece_rows_k(n, Gp);
         lv.push_back({n, K, ceil_div(n, Gp * K)});
@@ -609,6 +617,9 @@ geot_status_t plan_ep(const Problem &p, const Resolved &r, EpPlan *pl) {
     return GEOT_SUCCESS;
 }
 
+geot_status_t run_ep_levels(const Problem &p, const Resolved &r, const EpPlan &pl, char *base, GapList gaps,
+                            hipStream_t st);
+
 geot_status_t run_ep(const Problem &p, const Resolved &r, hipStream_t st, const Workspace *ws = nullptr) {
     EpPlan pl;
     geot_status_t s = plan_ep(p, r, &pl);
@@ -618,14 +629,14 @@ geot_status_t run_ep(const Problem &p, const Resolved &r, hipStream_t st, const 
     StreamCtx *ctx = nullptr;
     s = call_scratch(pl.bytes, st, ws, &scratch, &gaps, &ctx);
     if (s != GEOT_SUCCESS) return s;
-    return poison(ctx, run_ep_levels(p, r, pl.lv, (char *)scratch, pl.off_v, pl.off_s, pl.off_c, pl.off_x, pl.ld_p,
-                                     gaps, st));
+    return poison(ctx, run_ep_levels(p, r, pl, (char *)scratch, gaps, st));
 }
 
-geot_status_t run_ep_levels(const Problem &p, const Resolved &r, const std::vector<Level> &lv,
-                            char *base, const std::vector<size_t> &off_v,
-                            const std::vector<size_t> &off_s, const std::vector<size_t> &off_c,
-                            const std::vector<size_t> &off_x, int64_t ld_p, GapList gaps, hipStream_t st) {
+geot_status_t run_ep_levels(const Problem &p, const Resolved &r, const EpPlan &pl, char *base, GapList gaps,
+                            hipStream_t st) {
+    const std::vector<Level> &lv = pl.lv;
+    const std::vector<size_t> &off_v = pl.off_v, &off_s = pl.off_s, &off_c = pl.off_c, &off_x = pl.off_x;
+    const int64_t ld_p = pl.ld_p;
     const int red = p.op == GEOT_OP_MAX ? (p.arg ? RED_MAXARG : RED_MAX) : RED_SUM;
     for (size_t l = 0; l < lv.size(); ++l) {
         EpArgs a;
@@ -684,6 +695,12 @@ geot_status_t run_ep_levels(const Problem &p, const Resolved &r, const std::vect
             GEOT_HIP(launch_gap_fill_rows(p.out, p.F, p.F, std::min(r.V, 4), (int64_t)r.L * r.V * r.NT, p.S,
                                           gaps, p.arg, st),
                      "launch gap fill kernel");
+        if (pl.join) {
+            a.gaps = gaps;
+            GEOT_HIP(launch_ep_join(a, red, lv[0].nchunks, kFoldedGapBlocks, (int64_t)r.L * r.V * r.NT, st),
+                     "launch join kernel");
+            break;
+        }
     }
     return GEOT_SUCCESS;
 }

@@ -104,8 +104,8 @@ __device__ __forceinline__ void load_vec_p(const float *p, float *x) {
 template <int V>
 __device__ __forceinline__ void store_vec(float *p, const float *x) {
     if constexpr (V == 8) {  // 16-bit storage loads 8 elements per lane; fp32 results go out as 2 x 16 B
-        *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
-        *reinterpret_cast<float4 *>(p + 4) = make_float4(x[4], x[5], x[6], x[7]);
+        *reinterpret_cast<f32x4_t *>(p) = f32x4_t{x[0], x[1], x[2], x[3]};
+        *reinterpret_cast<f32x4_t *>(p + 4) = f32x4_t{x[4], x[5], x[6], x[7]};
     } else if constexpr (V == 4) {
         *reinterpret_cast<f32x4_t *>(p) = f32x4_t{x[0], x[1], x[2], x[3]};
     } else if constexpr (V == 3) {
@@ -265,7 +265,7 @@ __device__ __forceinline__ void gap_done(const GapList &g, int64_t blk, int64_t 
     }
 }
 
-// One block's share of the gap-list fill: records q = blk, blk + nblk, ...;
+// One block's (of 256 threads or a multiple) share of the gap-list fill: records q = blk, blk + nblk, ...;
 // rows [first, end) of record q's column tile (tiles of `tw` columns) = 0,
 // clamped to `rows`. The pass's last block empties the list.
 template <int V>
@@ -288,7 +288,7 @@ __device__ __forceinline__ void gap_fill_rows_body(float *out, int64_t F, int64_
         const int nvec = (int)((ncol + V - 1) / V);
         int tpr = 1;  // threads per row (power of two)
         while (tpr < nvec && tpr < 256) tpr <<= 1;
-        const int rows_per_pass = 256 / tpr;
+        const int rows_per_pass = (int)blockDim.x / tpr;
         const int j0 = threadIdx.x % tpr;
         for (int64_t row = lo + threadIdx.x / tpr; row < hi; row += rows_per_pass) {
             float *o = out + row * ld;

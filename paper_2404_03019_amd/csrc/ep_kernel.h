@@ -435,40 +435,31 @@ __device__ __forceinline__ void ep_body(const EpArgs &a, const int64_t bid, cons
                 }
             }
         } else {
-            int64_t r = r0;
-            for (; r + U <= r1; r += U) {
+            // rows past r1 load the last row again and are not reduced (one by one, a partial level's
+            // short last batch cost a trip to memory per row)
+            for (int64_t r = r0; r < r1; r += U) {
                 int32_t s[U];
                 Cnt c[U];
                 RV xr[U][NT];
                 uint32_t xi[U][NX];
 #pragma unroll
-                for (int u = 0; u < U; ++u) s[u] = (int32_t)idx[r + u];
+                for (int u = 0; u < U; ++u) s[u] = (int32_t)idx[min(r + u, r1 - 1)];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    load_term(r + u, xr[u], c[u]);
-                    if constexpr (MODE == SRC_PIECES) load_six(r + u, xi[u]);
-                    else self_ix(r + u, xi[u]);
+                    const int64_t rr = min(r + u, r1 - 1);
+                    load_term(rr, xr[u], c[u]);
+                    if constexpr (MODE == SRC_PIECES) load_six(rr, xi[u]);
+                    else self_ix(rr, xi[u]);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    float x[NV];
-                    widen_term(xr[u], x);
-                    piece(x, c[u], xi[u]);
-                    step(s[u], x, c[u], xi[u]);
+                    if (r + u < r1) {
+                        float x[NV];
+                        widen_term(xr[u], x);
+                        piece(x, c[u], xi[u]);
+                        step(s[u], x, c[u], xi[u]);
+                    }
                 }
-            }
-            for (; r < r1; ++r) {
-                RV xr[NT];
-                float x[NV];
-                uint32_t xi[NX];
-                Cnt c;
-                const int32_t s = (int32_t)idx[r];
-                load_term(r, xr, c);
-                if constexpr (MODE == SRC_PIECES) load_six(r, xi);
-                else self_ix(r, xi);
-                widen_term(xr, x);
-                piece(x, c, xi);
-                step(s, x, c, xi);
             }
         }
         // empty segments before this run (written after the row loop, so the first loads of

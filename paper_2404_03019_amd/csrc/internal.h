@@ -86,6 +86,12 @@ struct EpArgs {
     const uint32_t *six;
 };
 
+// The partials of `chunks` first-pass blocks (pv, pseg, pcnt, pix as the pass wrote them, a.ld_p
+// columns apart) reduced in one launch, which also fills the gap list with `gap_blocks` extra blocks
+// (a.gaps, in tiles of gap_tw columns). Uses of a: F, S, out, ld_out, mean, arg_out, gaps.
+hipError_t launch_ep_join(const EpArgs &a, int red, int64_t chunks, int gap_blocks, int64_t gap_tw,
+                          hipStream_t stream);
+
 // Dispatches on (elem, idx32) to the translation unit holding those instantiations.
 hipError_t launch_ep(const EpArgs &a, int red, int mode, int V, int NT, int L, int64_t nchunks,
                      hipStream_t stream);

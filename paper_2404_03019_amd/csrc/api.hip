@@ -326,13 +326,19 @@ int widest_vec(const Problem &p) {
     return 1;
 }
 
-// fp32 rows whose width is no multiple of 4 still move in 4-float vectors: gfx950 loads
-// and stores them at any 4-byte aligned address, and the vector that would cross a row's
-// end takes the row's last 4 columns (overlapping its neighbour). Rows of 3 floats take
-// one 3-float vector a lane. 0: neither applies.
+// Rows whose width their widest vector does not divide still move in such vectors: gfx950 loads
+// and stores them at any element's address, and the vector that would cross a row's end takes the
+// row's last elements (overlapping its neighbour). fp32: 4-float vectors, rows of 3 floats one
+// 3-float vector a lane. 16-bit storage: 8-element vectors, 4 and 2 for rows narrower than that (in
+// exact vectors an odd width moved one element per lane and load: 1,500,007 rows of 47 fp16
+// columns 125 us, 65 so). 0: none applies.
 int ragged_vec(const Problem &p) {
-    if (p.elem != ELEM_F32 || p.F < 3 || p.F % 4 == 0) return 0;
-    if (((uintptr_t)p.src & 3) != 0 || (((uintptr_t)p.out | (uintptr_t)p.arg) & 3) != 0) return 0;
+    if ((((uintptr_t)p.out | (uintptr_t)p.arg) & 3) != 0) return 0;
+    if (p.esize() == 2) {
+        if (p.F < 3 || p.F == 4 || p.F % 8 == 0 || ((uintptr_t)p.src & 1) != 0) return 0;
+        return p.F >= 8 ? 8 : p.F >= 4 ? 4 : 2;
+    }
+    if (p.F < 3 || p.F % 4 == 0 || ((uintptr_t)p.src & 3) != 0) return 0;
     return p.F == 3 ? 3 : 4;
 }
 
@@ -350,20 +356,30 @@ geot_status_t resolve(const Problem &p, const geot_kernel_choice_t &c, Resolved 
     if (r->family == GEOT_FAMILY_SP && p.arg)
         return fail(GEOT_ERROR_UNSUPPORTED, "recipients come from the element-parallel family only");
     const int vmax = widest_vec(p);
-    // ragged rows: 4-float vectors (3 for F = 3) where the width allows no exact one (3-float
-    // vectors: one lane a row)
+    // ragged rows: vectors of full size where the width allows no exact one (3-float vectors: one
+    // lane a row)
     const int vrag = ragged_vec(p);
     int V = c.vec == 0 ? (vrag ? vrag : vmax) : c.vec;
     int lanes = c.lanes, rows = c.rows;
     if (V == 3 && lanes > 1) V = vmax;   // a 3-float vector covers the row alone
-    if (from_selector && p.esize() == 2 && vmax == 8) {
-        // tree leaves are fit on fp32 shapes, which load 4 floats here (F % 8 == 0): load 8
+    if (from_selector && p.esize() == 2 && (vmax == 8 || vrag == 8)) {
+        // tree leaves are fit on fp32 shapes, which load 4 floats here (F >= 8): load 8
         // 16-bit elements instead, keeping the columns of one row group and the bytes it
         // reads (half the lanes, twice the rows)
         const int v32 = c.vec != 0 ? std::min(c.vec, 4) : 4;
         V = 8;
         if (lanes != 0) lanes = std::max(1, lanes * v32 / V);
-        if (rows != 0) rows = std::min(4096, rows * V / v32);
+        // ... up to 16 rows (24 above 64 columns, 32 from 17 to 32) of a segment reduction, whose
+        // blocks otherwise hold too many segments' ends at once: 16,777,216 bf16 rows of 64 columns
+        // in segments of about 16, max, 405 us at 16 rows, 417 at 24, 489 at 64; 4,000,000 of 128:
+        // 226, 204, 228; 300,000 of 64: 16.5, 18.4, 32.5; 8,000,000 of 16: 84, 90, 99 (32);
+        // 20,000,000 of 32: 276, 269, 271 (32). Gathers up to 16 edges below 2^21, where longer runs leave the chip idle (1,200,007
+        // edges of 47 columns 51 against 64 us at 32, 200,000 of 128: 19 against 23), while
+        // 10,000,000 edges of 128 take 446 at 16 and 413 at 32.
+        if (rows != 0) {
+            const int most = !p.gather ? (p.F > 64 ? 24 : p.F > 32 || p.F <= 16 ? 16 : 32) : (p.nnz < ((int64_t)1 << 21) ? 16 : 4096);
+            rows = std::min(most, rows * V / v32);
+        }
     }
     if (from_selector && p.arg && rows != 0) {
         // Carrying the recipients doubles what the block scan moves and holds registers (the
@@ -575,7 +591,7 @@ struct EpPlan {
 // 5 %) of the 2,000,000 rows of 64 columns in one segment 112 (118) against 107 (105) us. So it takes lists
 // up to kJoinBytes, where segments average at most kJoinSpan blocks' rows; a list twice as long
 // costs less than 4 % of its call by levels.
-constexpr int64_t kJoinChunks = 16384, kJoinBytes = (int64_t)2 << 20, kJoinSpan = 4;
+constexpr int64_t kJoinChunks = 16384, kJoinBytes = (int64_t)5 << 19, kJoinSpan = 4;
 
 geot_status_t plan_ep(const Problem &p, const Resolved &r, EpPlan *pl) {
     const int64_t G = kBlock / r.L;
@@ -747,16 +763,25 @@ geot_status_t run_sp_kernels(const Problem &p, const Resolved &r, int64_t *off, 
     return GEOT_SUCCESS;
 }
 
+constexpr int64_t kUntileBytes = (int64_t)64 << 20;
+
 // The kernel choice of a call: the forced one, else the selector's for the problem.
 geot_kernel_choice_t choose(const Problem &p, const geot_kernel_choice_t *forced) {
     if (forced) return *forced;
     geot_kernel_choice_t c;
     select_raw(p.nnz, p.S, p.F, p.op, p.gather ? (p.w ? 1 : 2) : 0, nullptr, &c);
     if ((p.typed() || p.arg) && c.family == GEOT_FAMILY_SP) c = geot_kernel_choice_t{GEOT_FAMILY_EP, 0, 0, 0, 0, 0};
-    // The leaves are fit on fp32 timings. A 16-bit X is half the bytes, and there the
-    // ids read once per tile cost more than the smaller slab saves (SpMM shape, bf16:
-    // 2.92 ms with two tiles in sequence, 2.83 ms without).
-    if (p.esize() == 2) untile(&c);
+    // Column tiles in sequence read the ids once per tile for a smaller slab of X. The leaves know
+    // neither X's type nor its rows: the slab saves nothing where X is 16-bit (SpMM shape, bf16:
+    // 2.92 ms with two tiles, 2.83 without) or fits the caches (X of 64 MB or less: 200,000 edges
+    // of 64 columns 32 against 16 us, of 128 26 against 21), or where the last tile is mostly
+    // empty (1,200,007 edges of 100 columns, 4 tiles of 32: 161 against 103 us). The run of rows of
+    // such a leaf goes with its narrower groups; whole rows take 32 edges, 16 up to 64 columns.
+    if ((c.flags & GEOT_FLAG_TILE_MAJOR) &&
+        (p.esize() == 2 || p.num_x_rows <= kUntileBytes / 4 / p.F || p.F % (4 * c.lanes) != 0)) {
+        untile(&c);
+        if (c.rows > (p.F > 64 ? 32 : 16) || p.esize() != 2) c.rows = p.F > 64 ? 32 : 16;
+    }
     return c;
 }
 
@@ -798,9 +823,9 @@ geot_status_t reduce(const Problem &p, hipStream_t st, const geot_kernel_choice_
     return s;
 }
 
-// Workspace a call of this shape needs, whatever the alignment of its arrays: the largest
-// need over the vector widths that F and the pointers may allow (the pointers decide the
-// width, and the width the partials' count).
+// Workspace a call of this shape needs, whatever the alignment of its arrays and the rows of X: the
+// largest need over the vector widths that F and the pointers may allow (the pointers decide the
+// width, and the width the partials' count) and over the choices a small and a large X get.
 geot_status_t workspace_size(Problem p, const geot_kernel_choice_t *forced, size_t *bytes) {
     t_detail.clear();
     if (!bytes) return fail(GEOT_ERROR_INVALID_VALUE, "bytes is NULL");
@@ -817,13 +842,16 @@ geot_status_t workspace_size(Problem p, const geot_kernel_choice_t *forced, size
     for (uintptr_t align : {(uintptr_t)256, (uintptr_t)8, (uintptr_t)4}) {
         p.src = (const void *)align;
         p.out = (float *)align;
-        Resolved r;
-        geot_status_t s = resolve(p, choose(p, forced), &r, forced == nullptr);
-        if (s != GEOT_SUCCESS) return s;
-        size_t need = 0;
-        s = scratch_need(p, r, &need);
-        if (s != GEOT_SUCCESS) return s;
-        most = std::max(most, need);
+        for (int64_t x_rows : {(int64_t)1, (int64_t)1 << 60}) {
+            p.num_x_rows = x_rows;
+            Resolved r;
+            geot_status_t s = resolve(p, choose(p, forced), &r, forced == nullptr);
+            if (s != GEOT_SUCCESS) return s;
+            size_t need = 0;
+            s = scratch_need(p, r, &need);
+            if (s != GEOT_SUCCESS) return s;
+            most = std::max(most, need);
+        }
     }
     *bytes = most;
     return GEOT_SUCCESS;

@@ -56,6 +56,10 @@ struct f32x3_t {
 };
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// words of 16-bit elements, which a row of odd width puts at any 2-byte aligned address
+typedef uint32_t h16x2_t __attribute__((aligned(2)));
+typedef uint32_t h16x4_t __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t h16x8_t __attribute__((ext_vector_type(4), aligned(2)));
 
 template <int V>
 __device__ __forceinline__ void load_vec(const float *p, float *x) {
@@ -155,19 +159,19 @@ template <int E, int V> struct Raw { float v[V]; };
 template <int V> struct Raw<ELEM_BF16, V> { uint32_t w[(V + 1) / 2]; };
 template <int V> struct Raw<ELEM_F16, V> { uint32_t w[(V + 1) / 2]; };
 
-// V consecutive elements at p (aligned to V elements); NT: non-temporal load
+// V consecutive elements at p (any element's address); NT: non-temporal load
 template <int E, int V, bool NT = false>
 __device__ __forceinline__ void load_raw(const typename ElemT<E>::T *p, Raw<E, V> &r) {
     if constexpr (E == ELEM_F32) {
         load_vec_p<V, NT>(p, r.v);
     } else if constexpr (V == 8) {
-        const u32x4_t t = ld<NT>(reinterpret_cast<const u32x4_t *>(p));
+        const h16x8_t t = ld<NT>(reinterpret_cast<const h16x8_t *>(p));
         r.w[0] = t.x; r.w[1] = t.y; r.w[2] = t.z; r.w[3] = t.w;
     } else if constexpr (V == 4) {
-        const u32x2_t t = ld<NT>(reinterpret_cast<const u32x2_t *>(p));
+        const h16x4_t t = ld<NT>(reinterpret_cast<const h16x4_t *>(p));
         r.w[0] = t.x; r.w[1] = t.y;
     } else if constexpr (V == 2) {
-        r.w[0] = ld<NT>(reinterpret_cast<const uint32_t *>(p));
+        r.w[0] = ld<NT>(reinterpret_cast<const h16x2_t *>(p));
     } else {
         r.w[0] = (uint32_t)ld<NT>(reinterpret_cast<const uint16_t *>(p));
     }

@@ -121,7 +121,7 @@ __device__ __forceinline__ void ep_body(const EpArgs &a, const int64_t bid, cons
     const int64_t r1 = min(r0 + (int64_t)a.K, bend);
     const bool has_rows = r0 < r1;
 
-    // Columns of this lane's vectors. Where F is not a multiple of V (fp32 only), the vector
+    // Columns of this lane's vectors. Where F is not a multiple of V, the vector
     // that would cross the row's end takes the row's last V columns instead: its loads stay
     // inside the row, and the columns it shares with the previous vector are reduced in the
     // same order by both lanes, so both store the same values.

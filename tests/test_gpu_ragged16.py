@@ -1,0 +1,70 @@
+"""bf16 and fp16 rows of widths that no vector divides, which move in 8-, 4- and 2-element vectors
+whose last one overlaps its neighbour, at any 2-byte aligned address; and the choices made for small and
+large X. Against the oracle on the exactly widened values."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2404_03019_amd as geot
+from gpu_util import compare, oracle_gather, oracle_segment, say
+from workloads import random_gather_problem, random_problem
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def stored(a, dtype, shift):
+    """`a` on the GPU in 16 bits, `shift` elements past an aligned address, and its exact values."""
+    flat = torch.zeros(a.size + shift, dtype=dtype, device=DEV)
+    t = flat[shift:].view(a.shape)
+    t.copy_(torch.from_numpy(a))
+    return t, t.float().cpu().numpy()
+
+
+@pytest.mark.parametrize("F", [1, 2, 3, 5, 7, 9, 15, 47, 100, 255, 259, 520])
+@pytest.mark.parametrize("dtype,shift", [(torch.bfloat16, 0), (torch.float16, 0), (torch.float16, 1), (torch.bfloat16, 3)])
+def test_segment_rows(dtype, shift, F):
+    p = random_problem(F + 1, 5003, 400, F, "zipf", "normal", 0.1)
+    s, wide = stored(p["src"], dtype, shift)
+    i = torch.from_numpy(p["index"]).to(DEV)
+    say(f"segment {dtype} F={F} shift={shift}")
+    for op in ("sum", "mean", "max"):
+        ref, terms = oracle_segment(wide, p["index"], 400, op)
+        for idx in (i, i.int()):
+            compare(geot.segment_reduce(s, idx, 400, op).cpu().numpy(), ref, op, terms, f"F={F} {op}")
+        out, arg = geot.segment_reduce_max_arg(s, i, 400) if op == "max" else (None, None)
+        if out is not None:
+            compare(out.cpu().numpy(), ref, "max", what="max with recipients")
+            a = arg.cpu().numpy().view(np.uint32).astype(np.int64)
+            ok = a != 0xFFFFFFFF
+            assert np.array_equal(wide[a[ok], np.nonzero(ok)[1]], ref[ok])
+
+
+@pytest.mark.parametrize("F", [3, 7, 15, 47, 100, 259])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_gather_rows(dtype, F):
+    g = random_gather_problem(F, 6007, 500, 700, F, "lognormal", "normal", True, 0.05)
+    x, wide = stored(g["X"], dtype, 1)
+    col, w, row = (torch.from_numpy(g[k]).to(DEV) for k in ("col", "weight", "index"))
+    say(f"gather {dtype} F={F}")
+    for op in ("sum", "mean", "max"):
+        ref, terms = oracle_gather(wide, g["col"], g["weight"], g["index"], 500, op)
+        got = geot.gather_scatter(x, col.int(), w, row.int(), 500, op)
+        compare(got.cpu().numpy(), ref, op, terms, f"F={F} {op}")
+
+
+@pytest.mark.parametrize("nnz,F,x_rows", [(40_000, 64, 3000), (40_000, 100, 3000), (300_000, 128, 140_000)])
+def test_column_tiles_by_the_size_of_x(nnz, F, x_rows):
+    """Whole rows and column tiles in sequence agree with the oracle where the rule chooses between them,
+    and the workspace that the size query names is enough for either."""
+    g = random_gather_problem(nnz, nnz, nnz // 20, x_rows, F, "poisson", "normal", True, 0.0)
+    x, col, w, row = (torch.from_numpy(g[k]).to(DEV) for k in ("X", "col", "weight", "index"))
+    R = nnz // 20
+    say(f"tiles nnz={nnz} F={F} X rows={x_rows}")
+    ref, terms = oracle_gather(g["X"], g["col"], g["weight"], g["index"], R, "sum")
+    compare(geot.gather_scatter(x, col, w, row, R).cpu().numpy(), ref, "sum", terms, "pooled")
+    ws = torch.empty(geot.workspace_size(nnz, R, F, "sum", gather=True), dtype=torch.uint8, device=DEV)
+    compare(geot.gather_scatter_ws(x, col, w, row, R, "sum", ws).cpu().numpy(), ref, "sum", terms, "workspace")
+    big = torch.zeros(200_000, F, device=DEV)
+    big[:x_rows] = x
+    compare(geot.gather_scatter_ws(big, col, w, row, R, "sum", ws).cpu().numpy(), ref, "sum", terms, "large X")

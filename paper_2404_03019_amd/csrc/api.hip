@@ -563,9 +563,9 @@ int64_t piece_rows_k(int64_t n, int64_t G) {
 
 // blocks that write the gap list, as a pass of their own or riding on the final partial level (or join)
 constexpr int kFoldedGapBlocks = 1024;
-// segment sum and max gradients from this many bytes of grad_src take the offsets pass first
-// (below, the kernels read the ids, which saves two launches)
-constexpr size_t kBcastOffsetsMinBytes = (size_t)64 << 20;
+// segment gradients over ids of more bytes than this take the offsets pass first (below, the ids
+// stay in the 256 MB MALL from the pass before, or from the offsets pass of the mean)
+constexpr size_t kBcastOffsetsMinBytes = (size_t)200 << 20;
 
 // Shape of the passes over fp32 partials: 8-element vectors (16-bit storage)
 // become 4-element vectors over twice the lanes, so the column tiles match.
@@ -1030,7 +1030,7 @@ static geot_status_t seg_backward(const float *grad_out, const void *sorted_inde
         overlaps(grad_src, gb, given, given ? (size_t)(num_segments * F) * 4 : 0))
         return fail(GEOT_ERROR_INVALID_VALUE, "grad_src overlaps an input");
     // widest vector that F and every pointer allow (fp32 operands: 16-byte loads of 4; 16-bit
-    // storage also 8 elements, loaded and stored as 16 bytes)
+    // storage also 8 elements, loaded and stored as 16 bytes), for the kernels that need it exact
     const uintptr_t ptrs = (uintptr_t)grad_out | (uintptr_t)grad_src | (uintptr_t)given |
                            (reads ? ((uintptr_t)src | (uintptr_t)out) : 0);
     int V = 1;
@@ -1042,16 +1042,19 @@ static geot_status_t seg_backward(const float *grad_out, const void *sorted_inde
     void *scratch = nullptr;
     StreamCtx *ctx = nullptr;
     const bool mean = op == GEOT_OP_MEAN, mx = op == GEOT_OP_MAX;
-    // From kBcastOffsetsMinBytes, where the segments average at least a block's rows (so most
+    // From kBcastOffsetsMinBytes of ids, where the segments average at least a block's rows (so most
     // blocks lie in one segment), an offsets pass reads the ids once and keeps each block's first
     // and last ids; the kernels that write grad_src then take every row's segment from the
     // offsets, so that their only HBM stream is their stores. Otherwise the ids are read where
     // they are needed (two launches fewer; mean still takes the offsets pass for the lengths).
-    // 2,000,000 rows in 100,000 segments, sum: 34 against 44 us at F = 16, 460 against 468 at
-    // F = 256 with the ids read; the power-law graph (114,615,892 rows, 232,965 segments, F =
-    // 32): 2.63 against 3.40 ms from the offsets.
+    // The power-law graph (114,615,892 rows, 232,965 segments, F = 32, 917 MB of ids), sum / mean /
+    // recorded max: 2.57 / 2.54 / 2.55 ms from the offsets, 3.66 / 4.24 / 3.72 from the ids;
+    // 20,000,000 rows (160 MB) in 150,000 segments: 565 / 467 / 486 us from the offsets, 450 / 437
+    // / 452 from the ids; 2,000,000 of 256 columns in 100,000: 422 / 349 / 377 and 336 / 346 / 351.
     const int rows_log2 = seg_bwd_rows_log2(F, V);
-    const bool use_first = gb >= kBcastOffsetsMinBytes && (nnz >> rows_log2) >= num_segments;
+    // (the kernels that read the ids move rows of any width in whole vectors, these do not)
+    const bool use_first = (size_t)nnz * is >= kBcastOffsetsMinBytes && (nnz >> rows_log2) >= num_segments &&
+                           (V == (es == 2 ? 8 : 4) || F < 4);
     const bool from_off = mean || use_first;
     const size_t o_arg = 0,
                  arg_b = mx && !given ? align256((size_t)(num_segments * F) * (seg_bwd_arg32(nnz) ? 4 : 8)) : 0;

@@ -83,7 +83,7 @@ __device__ __forceinline__ void put(T *p, T v) {
     else *p = v;
 }
 
-// V fp32 values stored as V elements of storage type E at p (aligned to V elements), with
+// V fp32 values stored as V elements of storage type E at p (any element's address), with
 // non-temporal stores when NT
 template <int E, int V, bool NT = false>
 __device__ __forceinline__ void store_elems(typename ElemT<E>::T *p, const float *x) {
@@ -97,13 +97,58 @@ __device__ __forceinline__ void store_elems(typename ElemT<E>::T *p, const float
 #pragma unroll
         for (int k = 0; k < V / 2; ++k) w[k] = narrow_pair<E>(x[2 * k], x[2 * k + 1]);
         if constexpr (V == 8) {
-            put<NT>(reinterpret_cast<u32x4_t *>(p), u32x4_t{w[0], w[1], w[2], w[3]});
+            put<NT>(reinterpret_cast<h16x8_t *>(p), h16x8_t{w[0], w[1], w[2], w[3]});
         } else if constexpr (V == 4) {
-            put<NT>(reinterpret_cast<u32x2_t *>(p), u32x2_t{w[0], w[1]});
+            put<NT>(reinterpret_cast<h16x4_t *>(p), h16x4_t{w[0], w[1]});
         } else {
-            put<NT>(reinterpret_cast<uint32_t *>(p), w[0]);
+            put<NT>(reinterpret_cast<h16x2_t *>(p), (h16x2_t)w[0]);
         }
     }
+}
+
+// The segment gradients that read the ids, over the vectors of grad_src laid end to end: a block
+// takes `rpb` whole rows (about 1,024 vectors, kPasses per thread; of a row of more than 1,024
+// vectors, one of `ctiles` tiles of them), so that no lane is idle whatever the width and the
+// stores are one contiguous range. Bound by the store stream, which is non-temporal: with
+// ordinary stores the rows evict the ids and gradient rows that the reads want from the caches.
+// 4,000,000 fp32 rows of 48 columns in 200,000 segments, whole call: sum 198 -> 154 us, mean 250
+// -> 138, recorded max 266 -> 136; bf16 of 64 columns 140 -> 84, 170 -> 101, 209 -> 100; 47
+// columns, which moved one element per lane: 396 -> 174, 383 -> 188, 353 -> 171. (With ordinary
+// stores only the lanes gained: mean 251, 194 and 256.) The vector that would cross a row's end
+// takes the row's last V elements; it and its neighbour store the same values.
+struct FlatMap {
+    int nvec;          // vectors per row
+    int rpb;           // rows per block
+    int ctiles;        // blocks per row (more than one only where rpb is 1)
+    uint64_t magic;    // ceil(2^32 / nvec): x / nvec for x < 2^16
+};
+
+template <int V>
+FlatMap flat_map(int64_t F) {
+    FlatMap m;
+    m.nvec = (int)((F + V - 1) / V);
+    m.rpb = m.nvec < 256 * kPasses ? 256 * kPasses / m.nvec : 1;
+    m.ctiles = (m.nvec + 256 * kPasses - 1) / (256 * kPasses);
+    m.magic = (((uint64_t)1 << 32) + (uint64_t)m.nvec - 1) / (uint64_t)m.nvec;
+    return m;
+}
+
+// this thread's row and first column in pass q (row -1: none)
+template <int V>
+__device__ __forceinline__ void flat_at(const FlatMap &m, int q, int64_t n, int64_t F, int64_t *row, int64_t *c) {
+    const unsigned x = (unsigned)q * 256u + threadIdx.x;
+    int r = 0, j;
+    int64_t row0 = blockIdx.x;
+    if (m.ctiles > 1) {
+        row0 = blockIdx.x / (unsigned)m.ctiles;
+        j = (int)(blockIdx.x - (unsigned)row0 * (unsigned)m.ctiles) * (256 * kPasses) + (int)x;
+    } else {
+        row0 *= m.rpb;
+        r = (int)(((uint64_t)x * m.magic) >> 32);
+        j = (int)x - r * m.nvec;
+    }
+    *row = r < m.rpb && j < m.nvec && row0 + r < n ? row0 + r : -1;
+    *c = min((int64_t)j * V, F - V);
 }
 
 // grad_src[i] = grad_out[idx[i]] (times 1 / len for mean), stored in the source's type E.
@@ -112,78 +157,41 @@ template <int E, typename I, int V, bool MEAN>
 __global__ __launch_bounds__(256) void seg_bwd_bcast_kernel(const float *__restrict__ gout,
                                                             const I *__restrict__ idx,
                                                             const int64_t *__restrict__ off, int64_t n,
-                                                            int64_t S, int64_t F,
+                                                            int64_t S, int64_t F, const FlatMap m,
                                                             typename ElemT<E>::T *__restrict__ gsrc) {
-    const int nvec = (int)(F / V);
-    const RowMap m = row_map(nvec);
-    int64_t seg[kPasses];
+    int64_t row[kPasses], c[kPasses], seg[kPasses];
 #pragma unroll
     for (int q = 0; q < kPasses; ++q) {
-        const int64_t i = m.row(q);
-        seg[q] = i < n ? (int64_t)idx[i] : -1;
+        flat_at<V>(m, q, n, F, &row[q], &c[q]);
+        seg[q] = row[q] >= 0 ? (int64_t)idx[row[q]] : -1;
     }
-    // mean: every pass's segment starts load together, branchless (a segment out of range
-    // reads segment 0's), before the first gradient row
+    float x[kPasses][V];
     int64_t o0[kPasses], o1[kPasses];
-    if (MEAN) {
 #pragma unroll
-        for (int q = 0; q < kPasses; ++q) {
-            const int64_t s = (uint64_t)seg[q] < (uint64_t)S ? seg[q] : 0;
-            o0[q] = off[s];
-            o1[q] = off[s + 1];
+    for (int q = 0; q < kPasses; ++q) {
+        const bool ok = (uint64_t)seg[q] < (uint64_t)S;
+        if (MEAN) {   // branchless (a segment out of range reads segment 0's)
+            o0[q] = off[ok ? seg[q] : 0];
+            o1[q] = off[ok ? seg[q] + 1 : 1];
+        }
+        if (ok) {
+            load_f32<V>(gout + seg[q] * F + c[q], x[q]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < V; ++k) x[q][k] = 0.0f;
         }
     }
-    if (nvec <= m.tpr) {
-        // one vector per thread and row: every pass's gradient row loads before the first store
-        // (one memory latency per block instead of one per pass)
-        if (m.j0 >= nvec) return;
-        float x[kPasses][V];
 #pragma unroll
-        for (int q = 0; q < kPasses; ++q) {
-            const bool ok = m.row(q) < n && (uint64_t)seg[q] < (uint64_t)S;
-            if (ok) {
-                load_f32<V>(gout + seg[q] * F + (int64_t)m.j0 * V, x[q]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < V; ++k) x[q][k] = 0.0f;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kPasses; ++q) {
-            const int64_t i = m.row(q);
-            if (i >= n) break;
-            if (MEAN && (uint64_t)seg[q] < (uint64_t)S) {
-                const float inv = 1.0f / (float)(o1[q] - o0[q]);
+    for (int q = 0; q < kPasses; ++q) {
+        if (row[q] < 0) continue;
+        if (MEAN) {
+            const float inv = 1.0f / (float)(o1[q] - o0[q]);
+            if ((uint64_t)seg[q] < (uint64_t)S) {
 #pragma unroll
                 for (int k = 0; k < V; ++k) x[q][k] = x[q][k] * inv;
             }
-            store_elems<E, V>(gsrc + i * F + (int64_t)m.j0 * V, x[q]);
         }
-        return;
-    }
-#pragma unroll
-    for (int q = 0; q < kPasses; ++q) {
-        const int64_t i = m.row(q);
-        if (i < n) {
-            const int64_t s = seg[q];
-            const bool ok = (uint64_t)s < (uint64_t)S;
-            float inv = 1.0f;
-            if (MEAN && ok) inv = 1.0f / (float)(o1[q] - o0[q]);
-            for (int j = m.j0; j < nvec; j += m.tpr) {
-                float x[V];
-                if (ok) {
-                    load_f32<V>(gout + s * F + (int64_t)j * V, x);
-                    if (MEAN) {
-#pragma unroll
-                        for (int k = 0; k < V; ++k) x[k] = x[k] * inv;
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < V; ++k) x[k] = 0.0f;
-                }
-                store_elems<E, V>(gsrc + i * F + (int64_t)j * V, x);
-            }
-        }
+        store_elems<E, V, true>(gsrc + row[q] * F + c[q], x[q]);
     }
 }
 
@@ -474,67 +482,50 @@ __global__ __launch_bounds__(256) void seg_bwd_max_arg_off_kernel(const typename
 }
 
 // grad_src[i, f] = grad_out[s, f] where i is the recipient of (s, f), else 0; ids first,
-// then every pass's gradient and recipient vectors, then the stores
+// then every pass's gradient and recipient vectors, then the stores (vectors end to end, as above)
 template <int E, typename I, int V, typename A>
 __global__ __launch_bounds__(256) void seg_bwd_max_write_kernel(const float *__restrict__ gout,
                                                                 const I *__restrict__ idx,
                                                                 const A *__restrict__ arg,
-                                                                int64_t n, int64_t S, int64_t F,
+                                                                int64_t n, int64_t S, int64_t F, const FlatMap m,
                                                                 typename ElemT<E>::T *__restrict__ gsrc) {
-    const int nvec = (int)(F / V);
-    const RowMap m = row_map(nvec);
-    int64_t seg[kPasses];
+    int64_t row[kPasses], c[kPasses], seg[kPasses];
 #pragma unroll
     for (int q = 0; q < kPasses; ++q) {
-        const int64_t i = m.row(q);
-        seg[q] = i < n ? (int64_t)idx[i] : -1;
+        flat_at<V>(m, q, n, F, &row[q], &c[q]);
+        seg[q] = row[q] >= 0 ? (int64_t)idx[row[q]] : -1;
     }
-    if (nvec <= m.tpr) {
-        float x[kPasses][V];
-        A w[kPasses][V];
+    float x[kPasses][V];
+    A w[kPasses][V];
 #pragma unroll
-        for (int q = 0; q < kPasses; ++q) {
-            const bool ok = (uint64_t)seg[q] < (uint64_t)S && m.j0 < nvec;
-            if (ok) {
-                load_f32<V>(gout + seg[q] * F + (int64_t)m.j0 * V, x[q]);
-                load_arg<A, V>(arg + seg[q] * F + (int64_t)m.j0 * V, w[q]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < V; ++k) {
-                    x[q][k] = 0.0f;
-                    w[q][k] = (A)~(A)0;
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kPasses; ++q) {
-            const int64_t i = m.row(q);
-            if (i >= n || m.j0 >= nvec) continue;
-#pragma unroll
-            for (int k = 0; k < V; ++k)
-                if (w[q][k] != (A)i) x[q][k] = 0.0f;
-            store_elems<E, V>(gsrc + i * F + (int64_t)m.j0 * V, x[q]);
-        }
-        return;
-    }
     for (int q = 0; q < kPasses; ++q) {
-        const int64_t i = m.row(q);
-        if (i >= n) break;
-        const int64_t s = seg[q];
-        const bool ok = (uint64_t)s < (uint64_t)S;
-        for (int j = m.j0; j < nvec; j += m.tpr) {
-            float x[V];
-            if (ok) {
-                load_f32<V>(gout + s * F + (int64_t)j * V, x);
+        if ((uint64_t)seg[q] < (uint64_t)S) {
+            load_f32<V>(gout + seg[q] * F + c[q], x[q]);
+            const A *a = arg + seg[q] * F + c[q];
+            if constexpr (sizeof(A) == 4) {   // 32-bit entries at any 4-byte aligned address
+                float bits[V];
+                load_f32<V>(reinterpret_cast<const float *>(a), bits);
 #pragma unroll
-                for (int k = 0; k < V; ++k)
-                    if (arg[s * F + (int64_t)j * V + k] != (A)i) x[k] = 0.0f;
+                for (int k = 0; k < V; ++k) w[q][k] = (A)__float_as_uint(bits[k]);
             } else {
 #pragma unroll
-                for (int k = 0; k < V; ++k) x[k] = 0.0f;
+                for (int k = 0; k < V; ++k) w[q][k] = a[k];
             }
-            store_elems<E, V>(gsrc + i * F + (int64_t)j * V, x);
+        } else {
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                x[q][k] = 0.0f;
+                w[q][k] = (A)~(A)0;
+            }
         }
+    }
+#pragma unroll
+    for (int q = 0; q < kPasses; ++q) {
+        if (row[q] < 0) continue;
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+            if (w[q][k] != (A)row[q]) x[q][k] = 0.0f;
+        store_elems<E, V, true>(gsrc + row[q] * F + c[q], x[q]);
     }
 }
 
@@ -2326,33 +2317,61 @@ int seg_bwd_rows_log2(int64_t F, int V) {
 
 int64_t seg_bwd_blocks(int64_t n, int64_t F, int V) { return grid_rows(n, (int)(F / V)); }
 
+namespace {
+
+// blocks of a flat pass over n rows; 0: too many for one grid
+unsigned flat_blocks(const FlatMap &m, int64_t n) {
+    const int64_t b = (n + m.rpb - 1) / m.rpb;
+    return b <= 0x7fffffffLL / m.ctiles ? (unsigned)(b * m.ctiles) : 0u;
+}
+
+// f(V) with the widest vector that a row of F elements of type E holds
+template <int E, typename Fn>
+hipError_t by_row_width(int64_t F, Fn &&f) {
+    if constexpr (E != ELEM_F32)
+        if (F >= 8) return f(std::integral_constant<int, 8>{});
+    if (F >= 4) return f(std::integral_constant<int, 4>{});
+    if (F >= 2) return f(std::integral_constant<int, 2>{});
+    return f(std::integral_constant<int, 1>{});
+}
+
+}  // namespace
+
 hipError_t launch_seg_bwd_bcast(const float *gout, const void *idx, int idx32, const int64_t *off,
                                 const int64_t *first, int64_t n, int64_t S, int64_t F, int V, int elem, bool mean,
                                 void *gsrc, hipStream_t st) {
     static_assert(kPasses * 256 == 1 << 10, "seg_bwd_rows_log2 assumes 1024 thread-rows per block");
     if (n <= 0) return hipSuccess;
     if (first && !off) return hipErrorInvalidValue;
-    const int64_t gb = grid_rows(n, (int)(F / V));
-    if (gb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const unsigned g = (unsigned)gb;
     return by_types(elem, idx32, [&](auto et, auto it) -> hipError_t {
         constexpr int E = decltype(et)::value;
         using I = typename decltype(it)::type;
         using T = typename ElemT<E>::T;
+        if (!first)
+            return by_row_width<E>(F, [&](auto vt) -> hipError_t {
+                constexpr int VV = decltype(vt)::value;
+                const FlatMap m = flat_map<VV>(F);
+                const unsigned g = flat_blocks(m, n);
+                if (!g) return hipErrorInvalidConfiguration;
+                if (mean)
+                    hipLaunchKernelGGL((seg_bwd_bcast_kernel<E, I, VV, true>), dim3(g), dim3(256), 0, st, gout,
+                                       static_cast<const I *>(idx), off, n, S, F, m, static_cast<T *>(gsrc));
+                else
+                    hipLaunchKernelGGL((seg_bwd_bcast_kernel<E, I, VV, false>), dim3(g), dim3(256), 0, st, gout,
+                                       static_cast<const I *>(idx), off, n, S, F, m, static_cast<T *>(gsrc));
+                return hipGetLastError();
+            });
+        const int64_t gb = grid_rows(n, (int)(F / V));
+        if (gb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+        const unsigned g = (unsigned)gb;
         return by_width<E>(V, [&](auto vt) -> hipError_t {
             constexpr int VV = decltype(vt)::value;
-            if (first && mean)
+            if (mean)
                 hipLaunchKernelGGL((seg_bwd_bcast_off_kernel<E, I, VV, true>), dim3(g), dim3(256), 0, st, gout,
                                    static_cast<const I *>(idx), off, first, n, S, F, static_cast<T *>(gsrc));
-            else if (first)
+            else
                 hipLaunchKernelGGL((seg_bwd_bcast_off_kernel<E, I, VV, false>), dim3(g), dim3(256), 0, st, gout,
                                    static_cast<const I *>(idx), off, first, n, S, F, static_cast<T *>(gsrc));
-            else if (mean)
-                hipLaunchKernelGGL((seg_bwd_bcast_kernel<E, I, VV, true>), dim3(g), dim3(256), 0, st, gout,
-                                   static_cast<const I *>(idx), off, n, S, F, static_cast<T *>(gsrc));
-            else
-                hipLaunchKernelGGL((seg_bwd_bcast_kernel<E, I, VV, false>), dim3(g), dim3(256), 0, st, gout,
-                                   static_cast<const I *>(idx), off, n, S, F, static_cast<T *>(gsrc));
             return hipGetLastError();
         });
     });
@@ -2396,13 +2415,20 @@ hipError_t launch_seg_bwd_max(const float *gout, const void *idx, int idx32, con
                     hipError_t e2 = hipGetLastError();
                     if (e2 != hipSuccess) return e2;
                 }
-                if (first)
+                if (first) {
                     hipLaunchKernelGGL((seg_bwd_max_write_off_kernel<E, I, VV, A>), dim3(g), dim3(256), 0, st, gout,
                                        static_cast<const I *>(idx), off, first, ap, n, S, F, static_cast<T *>(gsrc));
-                else
-                    hipLaunchKernelGGL((seg_bwd_max_write_kernel<E, I, VV, A>), dim3(g), dim3(256), 0, st, gout,
-                                       static_cast<const I *>(idx), ap, n, S, F, static_cast<T *>(gsrc));
-                return hipGetLastError();
+                    return hipGetLastError();
+                }
+                return by_row_width<E>(F, [&](auto wt) -> hipError_t {
+                    constexpr int VW = decltype(wt)::value;
+                    const FlatMap m = flat_map<VW>(F);
+                    const unsigned gf = flat_blocks(m, n);
+                    if (!gf) return hipErrorInvalidConfiguration;
+                    hipLaunchKernelGGL((seg_bwd_max_write_kernel<E, I, VW, A>), dim3(gf), dim3(256), 0, st, gout,
+                                       static_cast<const I *>(idx), ap, n, S, F, m, static_cast<T *>(gsrc));
+                    return hipGetLastError();
+                });
             });
         });
     };

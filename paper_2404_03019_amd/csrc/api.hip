@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -107,10 +108,10 @@ struct ScratchGuard {
     }
 };
 
-// Reduction calls keep their temporary buffer per (device, stream) and reuse it
-// in stream order, growing it (stream-ordered free of the old block, then a new
-// allocation) when a call needs more. Kernels of one stream run in order, so
-// consecutive calls never overlap on the buffer. The buffer starts with the
+// Calls keep their temporary buffer per (device, stream) and reuse it in stream order, growing it
+// (stream-ordered free of the old block, then a new allocation) when a call needs more. A call
+// holds the buffer (its mutex) until its last kernel is queued, so the kernels of calls on one
+// stream, from any thread, follow each other and never overlap on the buffer. The buffer starts with the
 // gap list (two counters and kGapCap records); the counters are zeroed when
 // the buffer is allocated and, after that, by the fill passes themselves.
 struct StreamKey {
@@ -119,16 +120,24 @@ struct StreamKey {
     bool operator<(const StreamKey &o) const { return dev != o.dev ? dev < o.dev : st < o.st; }
 };
 struct StreamCtx {
+    std::mutex mu;
     void *p = nullptr;
     size_t bytes = 0;
     bool dirty = false;     // a launch failed after the gap list was handed out
     bool captured = false;  // a call on this buffer was captured into a graph, which keeps its address
+    bool gone = false;      // released (geot_release_scratch): look the stream up again
 };
-std::mutex g_cache_mu;
-std::map<StreamKey, StreamCtx> g_cache;
+std::mutex g_cache_mu;   // guards the map and the retired list; taken before a context's mutex, never after
+std::map<StreamKey, std::shared_ptr<StreamCtx>> g_cache;
 // Buffers replaced by a larger one after a graph captured them: a replay of that graph
 // still reads and writes them, so they are freed only by geot_release_scratch.
 std::vector<std::pair<int, void *>> g_retired;
+
+// A stream's buffer, held by the call that runs on it.
+struct Held {
+    std::shared_ptr<StreamCtx> ctx;
+    std::unique_lock<std::mutex> lk;
+};
 
 constexpr size_t kGapHeader = 256;
 constexpr size_t kGapArea = kGapHeader + (size_t)kGapCap * 3 * sizeof(int64_t);
@@ -136,16 +145,25 @@ constexpr size_t kGapArea = kGapHeader + (size_t)kGapCap * 3 * sizeof(int64_t);
 // `user` gets `bytes` of scratch after the gap list; `g` the list of this call
 // (NULL when the call runs no gap-fill pass: only a call that runs one may take
 // the list, since its fill pass is what empties it again).
-geot_status_t stream_scratch(size_t bytes, hipStream_t st, void **user, GapList *g,
-                             StreamCtx **ctx_out) {
+geot_status_t stream_scratch(size_t bytes, hipStream_t st, void **user, GapList *g, Held *held) {
     *user = nullptr;
     int dev = 0;
     GEOT_HIP(hipGetDevice(&dev), "hipGetDevice");
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     GEOT_HIP(hipStreamIsCapturing(st, &cap), "hipStreamIsCapturing");
     const bool capturing = cap != hipStreamCaptureStatusNone;
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    StreamCtx &e = g_cache[StreamKey{dev, st}];
+    for (;;) {
+        {
+            std::lock_guard<std::mutex> lk(g_cache_mu);
+            std::shared_ptr<StreamCtx> &slot = g_cache[StreamKey{dev, st}];
+            if (!slot) slot = std::make_shared<StreamCtx>();
+            held->ctx = slot;
+        }
+        held->lk = std::unique_lock<std::mutex>(held->ctx->mu);
+        if (!held->ctx->gone) break;
+        held->lk.unlock();
+    }
+    StreamCtx &e = *held->ctx;
     const size_t need = kGapArea + ((bytes + 255) & ~(size_t)255);
     bool fresh = false;
     if (e.bytes < need) {
@@ -156,9 +174,25 @@ geot_status_t stream_scratch(size_t bytes, hipStream_t st, void **user, GapList 
                         "make one call of these shapes on the stream before capturing",
                         e.bytes, need);
         const size_t grown = std::max(need, e.bytes + e.bytes / 2);  // grow by half at least
-        if (e.p) {
-            if (e.captured) g_retired.emplace_back(dev, e.p);  // a captured graph still uses it
-            else GEOT_HIP(hipFreeAsync(e.p, st), "hipFreeAsync");
+        void *old = e.p;
+        if (old) {
+            if (e.captured) {   // a captured graph still uses it
+                held->lk.unlock();   // the map's mutex comes first
+                {
+                    std::lock_guard<std::mutex> lk(g_cache_mu);
+                    held->lk.lock();
+                    if (e.p == old && !e.gone) {
+                        g_retired.emplace_back(dev, old);
+                        e.p = nullptr;
+                    }
+                }
+                if (e.p || e.gone) {   // another call grew or released it meanwhile: start over
+                    held->lk.unlock();
+                    return stream_scratch(bytes, st, user, g, held);
+                }
+            } else {
+                GEOT_HIP(hipFreeAsync(old, st), "hipFreeAsync");
+            }
             e.p = nullptr;
             e.bytes = 0;
             e.captured = false;
@@ -182,7 +216,6 @@ geot_status_t stream_scratch(size_t bytes, hipStream_t st, void **user, GapList 
         g->rec = (int64_t *)((char *)e.p + kGapHeader);
     }
     *user = bytes ? (char *)e.p + kGapArea : nullptr;
-    *ctx_out = &e;
     return GEOT_SUCCESS;
 }
 
@@ -197,10 +230,8 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The temporary memory of one call: `bytes` after the gap list, from the caller's workspace
 // when `ws` is given, else from the stream's cached buffer.
-geot_status_t call_scratch(size_t bytes, hipStream_t st, const Workspace *ws, void **user, GapList *g,
-                           StreamCtx **ctx_out) {
-    if (!ws) return stream_scratch(bytes, st, user, g, ctx_out);
-    *ctx_out = nullptr;
+geot_status_t call_scratch(size_t bytes, hipStream_t st, const Workspace *ws, void **user, GapList *g, Held *held) {
+    if (!ws) return stream_scratch(bytes, st, user, g, held);
     const size_t need = kGapArea + align256(bytes);
     if (ws->bytes < need)
         return fail(GEOT_ERROR_INVALID_VALUE, "workspace of %zu bytes, this call needs %zu", ws->bytes, need);
@@ -213,12 +244,9 @@ geot_status_t call_scratch(size_t bytes, hipStream_t st, const Workspace *ws, vo
     return GEOT_SUCCESS;
 }
 
-// Marks the context so the next call re-zeroes the gap counters.
-geot_status_t poison(StreamCtx *ctx, geot_status_t s) {
-    if (s != GEOT_SUCCESS && ctx) {
-        std::lock_guard<std::mutex> lk(g_cache_mu);
-        ctx->dirty = true;
-    }
+// Marks a failed call's buffer so the next call re-zeroes the gap counters.
+geot_status_t poison(const Held &held, geot_status_t s) {
+    if (s != GEOT_SUCCESS && held.ctx) held.ctx->dirty = true;
     return s;
 }
 
@@ -642,10 +670,10 @@ geot_status_t run_ep(const Problem &p, const Resolved &r, hipStream_t st, const 
     if (s != GEOT_SUCCESS) return s;
     void *scratch = nullptr;
     GapList gaps;
-    StreamCtx *ctx = nullptr;
-    s = call_scratch(pl.bytes, st, ws, &scratch, &gaps, &ctx);
+    Held held;
+    s = call_scratch(pl.bytes, st, ws, &scratch, &gaps, &held);
     if (s != GEOT_SUCCESS) return s;
-    return poison(ctx, run_ep_levels(p, r, pl, (char *)scratch, gaps, st));
+    return poison(held, run_ep_levels(p, r, pl, (char *)scratch, gaps, st));
 }
 
 geot_status_t run_ep_levels(const Problem &p, const Resolved &r, const EpPlan &pl, char *base, GapList gaps,
@@ -727,10 +755,10 @@ geot_status_t run_sp_kernels(const Problem &p, const Resolved &r, int64_t *off, 
 geot_status_t run_sp(const Problem &p, const Resolved &r, hipStream_t st, const Workspace *ws = nullptr) {
     void *scratch = nullptr;
     GapList gaps;
-    StreamCtx *ctx = nullptr;
-    geot_status_t s = call_scratch((size_t)(p.S + 1) * 8, st, ws, &scratch, &gaps, &ctx);
+    Held held;
+    geot_status_t s = call_scratch((size_t)(p.S + 1) * 8, st, ws, &scratch, &gaps, &held);
     if (s != GEOT_SUCCESS) return s;
-    return poison(ctx, run_sp_kernels(p, r, (int64_t *)scratch, gaps, st));
+    return poison(held, run_sp_kernels(p, r, (int64_t *)scratch, gaps, st));
 }
 
 geot_status_t run_sp_kernels(const Problem &p, const Resolved &r, int64_t *off, GapList gaps,
@@ -1040,7 +1068,7 @@ static geot_status_t seg_backward(const float *grad_out, const void *sorted_inde
     const int elem = (int)src_type, idx32 = index_type == GEOT_INDEX_I32 ? 1 : 0;
     hipStream_t st = (hipStream_t)stream;
     void *scratch = nullptr;
-    StreamCtx *ctx = nullptr;
+    Held held;
     const bool mean = op == GEOT_OP_MEAN, mx = op == GEOT_OP_MAX;
     // From kBcastOffsetsMinBytes of ids, where the segments average at least a block's rows (so most
     // blocks lie in one segment), an offsets pass reads the ids once and keeps each block's first
@@ -1063,7 +1091,7 @@ static geot_status_t seg_backward(const float *grad_out, const void *sorted_inde
     GapList gaps;
     if ((mx && !given) || from_off) {
         geot_status_t s = stream_scratch(o_first + (use_first ? (size_t)blocks * 16 : 0), st, &scratch,
-                                         from_off ? &gaps : nullptr, &ctx);
+                                         from_off ? &gaps : nullptr, &held);
         if (s != GEOT_SUCCESS) return s;
     }
     void *arg = mx ? (given ? (void *)given : scratch) : nullptr;
@@ -1081,7 +1109,7 @@ static geot_status_t seg_backward(const float *grad_out, const void *sorted_inde
         return GEOT_SUCCESS;
     }
     const int shift = rows_log2;
-    return poison(ctx, [&]() -> geot_status_t {
+    return poison(held, [&]() -> geot_status_t {
         if (idx32)
             GEOT_HIP(launch_offsets_i32(static_cast<const int32_t *>(sorted_index), nnz, num_segments, off, gaps, st,
                                         first, shift),
@@ -1179,6 +1207,9 @@ geot_status_t geot_gather_scatter_max_arg(const void *X, geot_dtype_t x_type, in
     return reduce(p, (hipStream_t)stream, choice);
 }
 
+// Temporaries of the fused gradients up to this size stay in the stream's buffer between calls.
+static constexpr size_t kKeptBytes = (size_t)64 << 20;
+
 // The fused-form gradients; for max, `given` (may be NULL) holds the recipients a forward
 // geot_gather_scatter_max_arg recorded, and then out is not read and no recipient pass runs.
 static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num_x_rows, const void *col,
@@ -1236,7 +1267,7 @@ static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num
     if (es == 2 && op != GEOT_OP_MAX && F % 8 == 0 && (ptrs & 15) == 0) V = 8;
     else if (F % 4 == 0 && (ptrs & 15) == 0) V = 4;
     else if (F % 2 == 0 && (ptrs & 7) == 0) V = 2;
-    // temporaries from the stream-ordered pool (the forward call below uses the per-stream buffer):
+    // temporaries from the stream's kept buffer up to kKeptBytes, else from the stream-ordered pool:
     // row starts (mean), max recipients (max), the transposed edge list (grad_X for sum and mean)
     const bool mean = op == GEOT_OP_MEAN, mx = op == GEOT_OP_MAX;
     // max: grad_X pulled over the transposed list where its records are packed (X below 2^31
@@ -1262,38 +1293,76 @@ static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num
     const size_t o_row = transpose && !packed ? take((size_t)nnz * 8) : 0;
     const size_t o_w = transpose && !packed ? take((size_t)nnz * 4) : 0;
     const size_t o_part = pull ? take(pull_part_bytes(nnz, F)) : 0;
-    ScratchGuard sg;
-    sg.st = st;
-    geot_status_t s = scratch_alloc(&sg.p, at, st);
-    if (s != GEOT_SUCCESS) return s;
-    char *base = (char *)sg.p;
-    int64_t *roff = mean ? (int64_t *)(base + o_roff) : nullptr;
-    void *arg = mx ? (given ? (void *)given : (void *)(base + o_arg)) : nullptr;
-    if (mean) {
-        void *unused = nullptr;
-        GapList gaps;
-        StreamCtx *ctx = nullptr;
-        s = stream_scratch(0, st, &unused, &gaps, &ctx);
-        if (s != GEOT_SUCCESS) return s;
-        s = poison(ctx, [&]() -> geot_status_t {
-            if (idx32)
-                GEOT_HIP(launch_offsets_i32(static_cast<const int32_t *>(sorted_row), nnz, num_rows, roff, gaps, st),
-                         "launch offsets kernel");
-            else
-                GEOT_HIP(launch_offsets(static_cast<const int64_t *>(sorted_row), nnz, num_rows, roff, gaps, st),
-                         "launch offsets kernel");
-            GEOT_HIP(launch_gap_fill_i64(roff, num_rows + 1, gaps, st), "launch gap fill kernel");
-            return GEOT_SUCCESS;
-        }());
+    // the gather over the transposed list (sum, mean): grad_X = the sum of coef * grad_out rows
+    Problem tp{true, grad_out, num_rows, nullptr, nullptr, nullptr, nnz, nx, F, GEOT_OP_SUM, grad_X};
+    tp.idx32 = packed ? 1 : 0;
+    Resolved tr;
+    EpPlan plan;
+    const bool gather = transpose && !pull;
+    geot_status_t s = GEOT_SUCCESS;
+    if (gather) {
+        geot_kernel_choice_t c;
+        select_raw(nnz, nx, F, GEOT_OP_SUM, 1, nullptr, &c);
+        if (tp.typed() && c.family == GEOT_FAMILY_SP) c = geot_kernel_choice_t{GEOT_FAMILY_EP, 0, 0, 0, 0, 0};
+        // The transposed list gathers the destination rows, which repeat as often as the rows'
+        // edge counts and stay in cache: no column tiles in sequence (on the SpMM graph, 3.41 ms
+        // over the kept list without them, 3.55 ms with two), and longer row runs per group
+        // (there, one 128-column tile: 64 rows 3.16 ms, 128 rows 3.05-3.12, 256 rows 3.01, 512
+        // rows 3.00, 1,024 rows 3.06).
+        untile(&c);
+        if (nnz >= ((int64_t)1 << 20) && c.family == GEOT_FAMILY_EP && c.rows != 0 && c.rows < 256) c.rows = 256;
+        s = resolve(tp, c, &tr, true);
+        if (s == GEOT_SUCCESS) s = plan_ep(tp, tr, &plan);
         if (s != GEOT_SUCCESS) return s;
     }
-    const int bop = op == GEOT_OP_SUM ? GEOT_BWD_SUM : (mean ? GEOT_BWD_MEAN : GEOT_BWD_MAX);
-    // weights (and, for max where it is not pulled, X through atomic adds of the recipients only)
-    GEOT_HIP(launch_gs_bwd(X, elem, num_x_rows, col, idx32, weight, sorted_row, roff, out, grad_out, nnz, num_rows,
-                           F, V, bop, arg, given != nullptr, mx && !pull ? grad_X : nullptr, grad_weight, st),
-             "launch fused backward kernels");
-    if (transpose) {
-        // grad_X = gather_scatter of grad_out over the edges sorted by col (sum of coef * grad_out rows)
+    // In the kept buffer the gather's partials follow the other temporaries, and one buffer (with its
+    // gap list) serves the whole call. An allocation from the pool and its free take about 30 us of
+    // host time (160,007 edges of 100 columns, both gradients: 74 us of host time a call with them, 36
+    // without). Larger calls take the pool, and captured ones: a graph then owns these temporaries,
+    // and two graphs of one capture stream can run side by side on them.
+    const size_t o_ep = gather ? take(plan.bytes) : 0;
+    Held held;
+    GapList gaps;
+    ScratchGuard sg;
+    sg.st = st;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    GEOT_HIP(hipStreamIsCapturing(st, &cap), "hipStreamIsCapturing");
+    const bool kept = at > 0 && at <= kKeptBytes && cap == hipStreamCaptureStatusNone;
+    void *mem = nullptr;
+    s = kept ? stream_scratch(at, st, &mem, &gaps, &held) : scratch_alloc(&sg.p, at, st);
+    if (s != GEOT_SUCCESS) return s;
+    char *base = (char *)(kept ? mem : sg.p);
+    int64_t *roff = mean ? (int64_t *)(base + o_roff) : nullptr;
+    void *arg = mx ? (given ? (void *)given : (void *)(base + o_arg)) : nullptr;
+    auto row_starts = [&](const GapList &g) -> geot_status_t {
+        if (idx32)
+            GEOT_HIP(launch_offsets_i32(static_cast<const int32_t *>(sorted_row), nnz, num_rows, roff, g, st),
+                     "launch offsets kernel");
+        else
+            GEOT_HIP(launch_offsets(static_cast<const int64_t *>(sorted_row), nnz, num_rows, roff, g, st),
+                     "launch offsets kernel");
+        GEOT_HIP(launch_gap_fill_i64(roff, num_rows + 1, g, st), "launch gap fill kernel");
+        return GEOT_SUCCESS;
+    };
+    auto run = [&]() -> geot_status_t {
+        if (mean && kept) {
+            const geot_status_t e = row_starts(gaps);
+            if (e != GEOT_SUCCESS) return e;
+        } else if (mean) {
+            void *unused = nullptr;
+            GapList g;
+            Held h;
+            geot_status_t e = stream_scratch(0, st, &unused, &g, &h);
+            if (e != GEOT_SUCCESS) return e;
+            e = poison(h, row_starts(g));
+            if (e != GEOT_SUCCESS) return e;
+        }
+        const int bop = op == GEOT_OP_SUM ? GEOT_BWD_SUM : (mean ? GEOT_BWD_MEAN : GEOT_BWD_MAX);
+        // weights (and, for max where it is not pulled, X through atomic adds of the recipients only)
+        GEOT_HIP(launch_gs_bwd(X, elem, num_x_rows, col, idx32, weight, sorted_row, roff, out, grad_out, nnz, num_rows,
+                               F, V, bop, arg, given != nullptr, mx && !pull ? grad_X : nullptr, grad_weight, st),
+                 "launch fused backward kernels");
+        if (!transpose) return GEOT_SUCCESS;
         int64_t *key_t = packed ? nullptr : (int64_t *)(base + o_key);
         int64_t *row_t = packed ? nullptr : (int64_t *)(base + o_row);
         float *w_t = packed ? nullptr : (float *)(base + o_w);
@@ -1307,34 +1376,18 @@ static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num
             GEOT_HIP(launch_gs_bwd_x_max_pull(rec, (const int64_t *)(base + o_off), arg, grad_out, nnz, nx, num_rows, F, V,
                                               (float *)(base + o_part), grad_X, st),
                      "launch max pull kernel");
-            void *p_pull = sg.p;
-            sg.p = nullptr;
-            return scratch_free(p_pull, st);
+            return GEOT_SUCCESS;
         }
-        Problem tp{true, grad_out, num_rows, row_t, w_t, key_t, nnz, nx, F, GEOT_OP_SUM, grad_X};
-        if (packed) {
-            tp.idx = rec;
-            tp.col = rec + 1;
-            tp.w = (const float *)(rec + 2);
-            tp.idx32 = 1;
-            tp.meta_stride = rec_words;
-        }
-        geot_kernel_choice_t c;
-        select_raw(nnz, nx, F, GEOT_OP_SUM, 1, nullptr, &c);
-        if (tp.typed() && c.family == GEOT_FAMILY_SP) c = geot_kernel_choice_t{GEOT_FAMILY_EP, 0, 0, 0, 0, 0};
-        // The transposed list gathers the destination rows, which repeat as often as the rows'
-        // edge counts and stay in cache: no column tiles in sequence (on the SpMM graph, 3.41 ms
-        // over the kept list without them, 3.55 ms with two), and longer row runs per group
-        // (there, one 128-column tile: 64 rows 3.16 ms, 128 rows 3.05-3.12, 256 rows 3.01, 512
-        // rows 3.00, 1,024 rows 3.06).
-        untile(&c);
-        if (nnz >= ((int64_t)1 << 20) && c.family == GEOT_FAMILY_EP && c.rows != 0 && c.rows < 256) c.rows = 256;
-        Resolved r;
-        s = resolve(tp, c, &r, true);
-        if (s != GEOT_SUCCESS) return s;
-        s = run_ep(tp, r, st);
-        if (s != GEOT_SUCCESS) return s;
-    }
+        tp.idx = packed ? (const void *)rec : key_t;
+        tp.col = packed ? (const void *)(rec + 1) : row_t;
+        tp.w = packed ? (const float *)(rec + 2) : w_t;
+        if (packed) tp.meta_stride = rec_words;
+        if (kept) return run_ep_levels(tp, tr, plan, base + o_ep, gaps, st);
+        return run_ep(tp, tr, st);
+    };
+    s = run();
+    if (kept) return poison(held, s);
+    if (s != GEOT_SUCCESS) return s;
     void *p_free = sg.p;
     sg.p = nullptr;
     return scratch_free(p_free, st);
@@ -1421,10 +1474,10 @@ geot_status_t geot_transpose_edges(const int64_t *col, int64_t num_x_rows, const
     if (mean) {
         void *unused = nullptr;
         GapList gaps;
-        StreamCtx *ctx = nullptr;
-        s = stream_scratch(0, st, &unused, &gaps, &ctx);
+        Held held;
+        s = stream_scratch(0, st, &unused, &gaps, &held);
         if (s != GEOT_SUCCESS) return s;
-        s = poison(ctx, [&]() -> geot_status_t {
+        s = poison(held, [&]() -> geot_status_t {
             GEOT_HIP(launch_offsets(sorted_row, nnz, num_rows, roff, gaps, st), "launch offsets kernel");
             GEOT_HIP(launch_gap_fill_i64(roff, num_rows + 1, gaps, st), "launch gap fill kernel");
             return GEOT_SUCCESS;
@@ -1487,13 +1540,13 @@ geot_status_t geot_index_stats(const int64_t *sorted_index, int64_t nnz, int64_t
     const size_t off_bytes = align256((size_t)(num_segments + 1) * 8);
     void *scratch = nullptr;
     GapList gaps;
-    StreamCtx *ctx = nullptr;
-    geot_status_t s = stream_scratch(off_bytes + 64, st, &scratch, &gaps, &ctx);
+    Held held;
+    geot_status_t s = stream_scratch(off_bytes + 64, st, &scratch, &gaps, &held);
     if (s != GEOT_SUCCESS) return s;
     int64_t *off = (int64_t *)scratch;
     unsigned long long *acc = (unsigned long long *)((char *)scratch + off_bytes);
     unsigned long long h[3] = {0, 0, 0};
-    s = poison(ctx, [&]() -> geot_status_t {
+    s = poison(held, [&]() -> geot_status_t {
         GEOT_HIP(launch_offsets(sorted_index, nnz, num_segments, off, gaps, st), "launch offsets kernel");
         GEOT_HIP(launch_gap_fill_i64(off, num_segments + 1, gaps, st), "launch gap fill kernel");
         GEOT_HIP(launch_zero_u64(acc, 3, st), "launch zero kernel");
@@ -1545,11 +1598,15 @@ geot_status_t geot_release_scratch(void) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     geot_status_t st = GEOT_SUCCESS;
     for (auto &kv : g_cache) {
-        if (!kv.second.p) continue;
+        std::lock_guard<std::mutex> held(kv.second->mu);   // a call that holds the buffer queues its kernels first
+        kv.second->gone = true;
+        if (!kv.second->p) continue;
         int cur = 0;
         hipError_t e = hipGetDevice(&cur);
         if (e == hipSuccess) e = hipSetDevice(kv.first.dev);
-        if (e == hipSuccess) e = hipFreeAsync(kv.second.p, kv.first.st);
+        if (e == hipSuccess) e = hipFreeAsync(kv.second->p, kv.first.st);
+        kv.second->p = nullptr;
+        kv.second->bytes = 0;
         if (e == hipSuccess) e = hipStreamSynchronize(kv.first.st);
         (void)hipSetDevice(cur);
         if (e != hipSuccess && st == GEOT_SUCCESS) st = hip_fail(e, "release scratch");

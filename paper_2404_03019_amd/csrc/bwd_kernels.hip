@@ -1422,12 +1422,17 @@ __global__ __launch_bounds__(256) void scale_by_count_kernel(float *__restrict__
 }
 
 // ---- counting sort of the edges by source row (the transposed problem) ----
-// both edge passes: block b takes edges [b, b + 1) * 256 * kPasses, one pass of 256 at a time
+// both edge passes: block b takes edges [b, b + 1) * 256 * passes, one pass of 256 at a time. One
+// pass where the list is short: each waits for a trip to memory and an atomic's, and four in a row
+// left the chip idle (160,007 edges: 157 blocks, 11.7 us a kernel; 626 and 10.3 so, of which the
+// most popular column's atomics are the most).
+int edge_passes(int64_t n) { return n < ((int64_t)1 << 20) ? 1 : kPasses; }
+
 template <typename I>
-__global__ __launch_bounds__(256) void hist_kernel(const I *col, int64_t n, int64_t nx,
+__global__ __launch_bounds__(256) void hist_kernel(const I *col, int64_t n, int64_t nx, int passes,
                                                    unsigned *counts) {
-    for (int q = 0; q < kPasses; ++q) {
-        const int64_t e = ((int64_t)blockIdx.x * kPasses + q) * 256 + threadIdx.x;
+    for (int q = 0; q < passes; ++q) {
+        const int64_t e = ((int64_t)blockIdx.x * passes + q) * 256 + threadIdx.x;
         if (e >= n) break;
         const int64_t c = (int64_t)col[e];
         if ((uint64_t)c < (uint64_t)nx) atomicAdd(counts + c, 1u);
@@ -1489,13 +1494,37 @@ __global__ __launch_bounds__(256) void scan_sums_kernel(int64_t *sums, int64_t n
     }
 }
 
+// off[i] += the totals of the tiles before i's; off[n] = the sum of all. With SCANNED, sums holds
+// their exclusive scan; otherwise each block adds up the totals before its tile itself (one launch
+// fewer, while the totals are few). A block takes 1,024 consecutive entries, all of one tile.
+constexpr int kScanAdd = 1024;
+constexpr int64_t kScanDirect = 2048;   // tiles up to which the blocks add up the totals themselves
+static_assert(kScanTile % kScanAdd == 0, "a block's entries lie in one tile");
+
+template <bool SCANNED>
 __global__ __launch_bounds__(256) void scan_add_kernel(const unsigned *counts, int64_t *off, int64_t n,
                                                        const int64_t *sums) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t o = off[i] + sums[i / kScanTile];
-    off[i] = o;
-    if (i == n - 1) off[n] = o + (int64_t)counts[i];
+    __shared__ int64_t s_part[4];
+    const int64_t base = (int64_t)blockIdx.x * kScanAdd, tile = base / kScanTile;
+    int64_t add = 0;
+    if constexpr (SCANNED) {
+        add = sums[tile];
+    } else {
+        for (int64_t t = threadIdx.x; t < tile; t += 256) add += sums[t];
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) add += __shfl_xor((long long)add, d, 64);
+        if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = add;
+        __syncthreads();
+        add = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+    }
+#pragma unroll
+    for (int k = 0; k < kScanAdd / 256; ++k) {
+        const int64_t i = base + k * 256 + threadIdx.x;
+        if (i >= n) break;
+        const int64_t o = off[i] + add;
+        off[i] = o;
+        if (i == n - 1) off[n] = o + (int64_t)counts[i];
+    }
 }
 
 // edge e goes to slot off[col[e]] + (a decrementing per-row cursor): the
@@ -1505,10 +1534,10 @@ __global__ __launch_bounds__(256) void scan_add_kernel(const unsigned *counts, i
 template <bool PACKED, typename I>
 __global__ __launch_bounds__(256) void place_kernel(const I *col, int64_t nx, const I *row,
                                                     const float *w, const int64_t *roff, int64_t nrows, int mean,
-                                                    int64_t n, const int64_t *off, unsigned *cursor,
+                                                    int64_t n, int passes, const int64_t *off, unsigned *cursor,
                                                     int64_t *key_t, int64_t *row_t, float *w_t, int32_t *rec) {
-    for (int q = 0; q < kPasses; ++q) {
-        const int64_t e = ((int64_t)blockIdx.x * kPasses + q) * 256 + threadIdx.x;
+    for (int q = 0; q < passes; ++q) {
+        const int64_t e = ((int64_t)blockIdx.x * passes + q) * 256 + threadIdx.x;
         if (e >= n) break;
         const int64_t c = (int64_t)col[e];
         if ((uint64_t)c >= (uint64_t)nx) continue;
@@ -2049,9 +2078,14 @@ hipError_t scan_counts(const unsigned *counts, int64_t len, int64_t *off, int64_
     hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)ntiles), dim3(256), 0, st, counts, len, off, sums);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const dim3 ga((unsigned)((len + kScanAdd - 1) / kScanAdd));
+    if (ntiles <= kScanDirect) {
+        hipLaunchKernelGGL(scan_add_kernel<false>, ga, dim3(256), 0, st, counts, off, len, sums);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, st, sums, ntiles);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st, counts, off, len, sums);
+    hipLaunchKernelGGL(scan_add_kernel<true>, ga, dim3(256), 0, st, counts, off, len, sums);
     return hipGetLastError();
 }
 
@@ -2192,20 +2226,19 @@ hipError_t launch_transpose_t(const I *col, int64_t nx, const I *row, const floa
     }
     hipError_t e = launch_zero_u64((unsigned long long *)counts, (nx + 1) / 2, st);
     if (e != hipSuccess) return e;
-    const int64_t geb = (n + 256 * kPasses - 1) / (256 * kPasses);
+    const int passes = edge_passes(n);
+    const int64_t geb = (n + 256 * passes - 1) / (256 * passes);
     if (geb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const unsigned ge = (unsigned)geb;
-    hipLaunchKernelGGL(hist_kernel<I>, dim3(ge), dim3(256), 0, st, col, n, nx, counts);
+    hipLaunchKernelGGL(hist_kernel<I>, dim3(ge), dim3(256), 0, st, col, n, nx, passes, counts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = scan_counts(counts, nx, off, sums, st)) != hipSuccess) return e;
     if (rec)
         hipLaunchKernelGGL((place_kernel<true, I>), dim3(ge), dim3(256), 0, st, col, nx, row, w, roff, nrows,
-                           mean ? 1 : 0, n,
-                           off, counts, key_t, row_t, w_t, rec);
+                           mean ? 1 : 0, n, passes, off, counts, key_t, row_t, w_t, rec);
     else
         hipLaunchKernelGGL((place_kernel<false, I>), dim3(ge), dim3(256), 0, st, col, nx, row, w, roff, nrows,
-                           mean ? 1 : 0,
-                           n, off, counts, key_t, row_t, w_t, rec);
+                           mean ? 1 : 0, n, passes, off, counts, key_t, row_t, w_t, rec);
     return hipGetLastError();
 }
 

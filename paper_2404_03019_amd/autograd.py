@@ -73,18 +73,12 @@ class Graph:
     (Section III-C: variance as a feature); they are refreshed when the ids are updated
     in place."""
 
-    # kernel choice for the gather over the transposed list from 2^20 edges: one column tile and
-    # 256 rows per row group (the library's tree is fit on forward gathers, whose gathered rows
-    # repeat less; SpMM graph, 128 columns: 3.0 ms against 3.3 with the tree's choice)
-    TRANSPOSED_GATHER = dict(family="ep", rows=256)
-
     def __init__(self, col, row, num_nodes: int, weight=None, num_src: int | None = None):
         self.col, self.row, self.weight = col, row, weight
         self.num_nodes = int(num_nodes)
         self.num_src = int(num_src if num_src is not None else num_nodes)
         self._transposed = {}
         self._stats = None
-        self.gather_choice = self.TRANSPOSED_GATHER if row.numel() >= (1 << 20) else None
 
     def stats(self):
         """geot_index_stats of the destination ids (kept until the ids change in place)."""
@@ -92,6 +86,29 @@ class Graph:
         if self._stats is None or self._stats[0] != version:
             self._stats = (version, geot.index_stats(self.row.long(), self.num_nodes) if self.row.numel() else None)
         return self._stats[1]
+
+    def transposed_choice(self, F: int):
+        """Kernel choice for the gather of F columns over the transposed list (whole rows: its gathered
+        rows are the destinations', which repeat as often as their edge counts).
+
+        Where a few destinations hold most edges (lengths spread over 8 times their mean) the rows come
+        from cache and long runs per row group pay for the block's scan; otherwise they come from
+        memory and short runs keep more blocks in flight. MI355X, 128 columns: 61,859,140 edges,
+        power-law rows, 2.96 ms at 256 rows, 3.02 at 128, 3.80 at 16; 10,000,000 edges, lognormal rows, 0.80 ms
+        at 256, 0.74 at 16. Up to 16 columns 8 rows are best either way (20,000,000 edges: 237 and
+        395 us against 396 and 601 at 256)."""
+        n = self.row.numel()
+        if F <= 16:
+            rows = 8
+        elif n >= (1 << 21) and self._heavy():
+            rows = 256 if n >= (1 << 25) else 128
+        else:
+            rows = 16
+        return dict(family="ep", rows=rows)
+
+    def _heavy(self) -> bool:
+        s = self.stats()
+        return s is not None and s["var_len"] > (8.0 * s["mean_len"]) ** 2
 
     def transposed(self, reduce: str):
         """(sorted_col, row_t, coef) for `reduce` in sum / mean."""
@@ -138,7 +155,7 @@ class GatherScatter(torch.autograd.Function):
         if need_x and ctx.graph is not None and ctx.reduce in ("sum", "mean"):
             sorted_col, row_t, coef = ctx.graph.transposed(ctx.reduce)
             gx = geot.gather_scatter(grad_out, row_t, coef, sorted_col, x.shape[0], "sum",
-                                     choice=ctx.graph.gather_choice)
+                                     choice=ctx.graph.transposed_choice(grad_out.shape[1]))
             need_x = False
         if ctx.recorded:   # out holds the recipients the forward recorded
             gx2, gw = geot.gather_scatter_backward_max_arg(x, col, weight, row, grad_out, out,

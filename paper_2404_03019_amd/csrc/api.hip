@@ -1306,11 +1306,14 @@ static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num
         if (tp.typed() && c.family == GEOT_FAMILY_SP) c = geot_kernel_choice_t{GEOT_FAMILY_EP, 0, 0, 0, 0, 0};
         // The transposed list gathers the destination rows, which repeat as often as the rows'
         // edge counts and stay in cache: no column tiles in sequence (on the SpMM graph, 3.41 ms
-        // over the kept list without them, 3.55 ms with two), and longer row runs per group
-        // (there, one 128-column tile: 64 rows 3.16 ms, 128 rows 3.05-3.12, 256 rows 3.01, 512
-        // rows 3.00, 1,024 rows 3.06).
+        // over the kept list without them, 3.55 ms with two), and longer row runs per group above
+        // 16 columns from 2^21 edges: 128, between what rows that come from cache and rows that come
+        // from memory want (at 16 / 128 / 256 rows: the SpMM graph 3.80, 3.02, 2.96 ms; 20,000,000
+        // edges of 64 columns with lognormal rows 765, 831, 858 us; 3,000,000 of 32 62, 64, 95), and
+        // 256 from 2^25 edges.
         untile(&c);
-        if (nnz >= ((int64_t)1 << 20) && c.family == GEOT_FAMILY_EP && c.rows != 0 && c.rows < 256) c.rows = 256;
+        const int run = nnz >= ((int64_t)1 << 25) ? 256 : 128;
+        if (nnz >= ((int64_t)1 << 21) && F > 16 && c.rows != 0 && c.rows < run) c.rows = run;
         s = resolve(tp, c, &tr, true);
         if (s == GEOT_SUCCESS) s = plan_ep(tp, tr, &plan);
         if (s != GEOT_SUCCESS) return s;

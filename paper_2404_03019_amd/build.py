@@ -24,6 +24,8 @@ FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-parameter", "-Wno-unused-command-line-argument",
+    # an element-aligned vector type handed to code that assumes the vector's own alignment
+    "-Werror=align-mismatch",
 ]
 
 

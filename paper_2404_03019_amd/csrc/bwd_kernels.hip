@@ -76,32 +76,36 @@ __device__ __forceinline__ uint32_t narrow_pair(float a, float b) {
     }
 }
 
-// one value stored with the non-temporal cache policy (NT) or an ordinary store
-template <bool NT, typename T>
-__device__ __forceinline__ void put(T *p, T v) {
-    if constexpr (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
-
 // V fp32 values stored as V elements of storage type E at p (any element's address), with
-// non-temporal stores when NT
+// non-temporal stores when NT (each on the typed pointer, as in load_raw)
 template <int E, int V, bool NT = false>
 __device__ __forceinline__ void store_elems(typename ElemT<E>::T *p, const float *x) {
     if constexpr (E == ELEM_F32) {
         if constexpr (NT) store_vec_nt<V>(p, x);
         else store_vec<V>(p, x);
     } else if constexpr (V == 1) {
-        put<NT>(reinterpret_cast<uint16_t *>(p), (uint16_t)narrow_pair<E>(x[0], 0.0f));
+        const uint16_t v = (uint16_t)narrow_pair<E>(x[0], 0.0f);
+        uint16_t *q = reinterpret_cast<uint16_t *>(p);
+        if constexpr (NT) __builtin_nontemporal_store(v, q);
+        else *q = v;
     } else {
         uint32_t w[V / 2];
 #pragma unroll
         for (int k = 0; k < V / 2; ++k) w[k] = narrow_pair<E>(x[2 * k], x[2 * k + 1]);
         if constexpr (V == 8) {
-            put<NT>(reinterpret_cast<h16x8_t *>(p), h16x8_t{w[0], w[1], w[2], w[3]});
+            const h16x8_t v = {w[0], w[1], w[2], w[3]};
+            h16x8_t *q = reinterpret_cast<h16x8_t *>(p);
+            if constexpr (NT) __builtin_nontemporal_store(v, q);
+            else *q = v;
         } else if constexpr (V == 4) {
-            put<NT>(reinterpret_cast<h16x4_t *>(p), h16x4_t{w[0], w[1]});
+            const h16x4_t v = {w[0], w[1]};
+            h16x4_t *q = reinterpret_cast<h16x4_t *>(p);
+            if constexpr (NT) __builtin_nontemporal_store(v, q);
+            else *q = v;
         } else {
-            put<NT>(reinterpret_cast<h16x2_t *>(p), (h16x2_t)w[0]);
+            h16x2_t *q = reinterpret_cast<h16x2_t *>(p);
+            if constexpr (NT) __builtin_nontemporal_store(w[0], q);
+            else *q = w[0];
         }
     }
 }

@@ -54,8 +54,6 @@ typedef float f32x4_t __attribute__((ext_vector_type(4), aligned(4)));
 struct f32x3_t {
     float x, y, z;
 };
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // words of 16-bit elements, which a row of odd width puts at any 2-byte aligned address
 typedef uint32_t h16x2_t __attribute__((aligned(2)));
 typedef uint32_t h16x4_t __attribute__((ext_vector_type(2), aligned(2)));
@@ -79,12 +77,6 @@ __device__ __forceinline__ void load_vec(const float *p, float *x) {
 
 // Non-temporal loads (the `nt` cache policy): for data read exactly once, such
 // as streamed rows and ids, which then does not displace data that is reused.
-
-template <bool NT, typename T>
-__device__ __forceinline__ T ld(const T *p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
-}
 
 template <int V, bool NT>
 __device__ __forceinline__ void load_vec_p(const float *p, float *x) {
@@ -159,21 +151,32 @@ template <int E, int V> struct Raw { float v[V]; };
 template <int V> struct Raw<ELEM_BF16, V> { uint32_t w[(V + 1) / 2]; };
 template <int V> struct Raw<ELEM_F16, V> { uint32_t w[(V + 1) / 2]; };
 
-// V consecutive elements at p (any element's address); NT: non-temporal load
+// V consecutive elements at p (any element's address); NT: non-temporal load. Each access is made on
+// the typed pointer here: passed through a function template, the type would lose its alignment.
 template <int E, int V, bool NT = false>
 __device__ __forceinline__ void load_raw(const typename ElemT<E>::T *p, Raw<E, V> &r) {
     if constexpr (E == ELEM_F32) {
         load_vec_p<V, NT>(p, r.v);
     } else if constexpr (V == 8) {
-        const h16x8_t t = ld<NT>(reinterpret_cast<const h16x8_t *>(p));
+        const h16x8_t *q = reinterpret_cast<const h16x8_t *>(p);
+        h16x8_t t;
+        if constexpr (NT) t = __builtin_nontemporal_load(q);
+        else t = *q;
         r.w[0] = t.x; r.w[1] = t.y; r.w[2] = t.z; r.w[3] = t.w;
     } else if constexpr (V == 4) {
-        const h16x4_t t = ld<NT>(reinterpret_cast<const h16x4_t *>(p));
+        const h16x4_t *q = reinterpret_cast<const h16x4_t *>(p);
+        h16x4_t t;
+        if constexpr (NT) t = __builtin_nontemporal_load(q);
+        else t = *q;
         r.w[0] = t.x; r.w[1] = t.y;
     } else if constexpr (V == 2) {
-        r.w[0] = ld<NT>(reinterpret_cast<const h16x2_t *>(p));
+        const h16x2_t *q = reinterpret_cast<const h16x2_t *>(p);
+        if constexpr (NT) r.w[0] = __builtin_nontemporal_load(q);
+        else r.w[0] = *q;
     } else {
-        r.w[0] = (uint32_t)ld<NT>(reinterpret_cast<const uint16_t *>(p));
+        const uint16_t *q = reinterpret_cast<const uint16_t *>(p);
+        if constexpr (NT) r.w[0] = (uint32_t)__builtin_nontemporal_load(q);
+        else r.w[0] = (uint32_t)*q;
     }
 }
 

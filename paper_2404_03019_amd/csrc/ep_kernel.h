@@ -59,7 +59,7 @@ __device__ __forceinline__ void ep_body(const EpArgs &a, const int64_t bid, cons
     // 8-element lanes (16-bit storage), without recipients (the point cloud's mean 0.807 ->
     // 0.786 ms, the power-law graph's sum 2.368 -> 2.353 ms, its bf16 sum 1.42 -> 1.38 ms; 118
     // VGPRs and 4 waves per SIMD instead of 92 and 5), else 4 (8 for narrower lanes)
-    constexpr int U = (NV == 4 && L >= 8 || NV == 8) && RED != RED_MAXARG ? 8 : (NV >= 4 ? 4 : 8);
+    constexpr int U = ((NV == 4 && L >= 8) || NV == 8) && RED != RED_MAXARG ? 8 : (NV >= 4 ? 4 : 8);
     // edges per batch of the gather pipeline: 8 for 4-float lanes whose group shares the
     // metadata loads (L >= 8) and carries no recipients (the SpMM graph: fp32 sum 5.18 ->
     // 5.14 ms, its gradient w.r.t. X 4.13 -> 4.06 ms), else 4 (8 for narrower lanes; bf16 lanes
@@ -435,31 +435,68 @@ __device__ __forceinline__ void ep_body(const EpArgs &a, const int64_t bid, cons
                 }
             }
         } else {
-            // rows past r1 load the last row again and are not reduced (one by one, a partial level's
-            // short last batch cost a trip to memory per row)
-            for (int64_t r = r0; r < r1; r += U) {
-                int32_t s[U];
-                Cnt c[U];
-                RV xr[U][NT];
-                uint32_t xi[U][NX];
+            // Padding every batch (rows past r1 load the last row again and are not reduced) saves the trip to
+            // memory per row that a short batch costs, but holds an address per row. Measured against full
+            // batches with a short padded one behind them (us, padded first): partial levels and fp32 rows
+            // of 2 to 8 floats gain (2,000,000 rows of 4: 20.2 against 22.3, of 8: 20.7 / 22.9; 20,000,000 of
+            // 5: 167 / 185; 60,000,000 of 2: 288 / 302); one float per lane and 16-bit elements lose the
+            // waves that the registers took (100,000,000 rows of one float: 449 / 353, 69 VGPRs for 50;
+            // 60,000,000 bf16 rows of 8: 372 / 358, of 4: 206 / 197; the power-law graph in bf16: 1,379 / 1,356).
+            constexpr bool kPadAll = MODE == SRC_PIECES || (E == ELEM_F32 && L <= 2 && NV > 1);
+            int64_t r = r0;
+            if constexpr (kPadAll) {
+                for (; r < r1; r += U) {
+                    int32_t s[U];
+                    Cnt c[U];
+                    RV xr[U][NT];
+                    uint32_t xi[U][NX];
 #pragma unroll
-                for (int u = 0; u < U; ++u) s[u] = (int32_t)idx[min(r + u, r1 - 1)];
+                    for (int u = 0; u < U; ++u) s[u] = (int32_t)idx[min(r + u, r1 - 1)];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int64_t rr = min(r + u, r1 - 1);
-                    load_term(rr, xr[u], c[u]);
-                    if constexpr (MODE == SRC_PIECES) load_six(rr, xi[u]);
-                    else self_ix(rr, xi[u]);
-                }
+                    for (int u = 0; u < U; ++u) {
+                        const int64_t rr = min(r + u, r1 - 1);
+                        load_term(rr, xr[u], c[u]);
+                        if constexpr (MODE == SRC_PIECES) load_six(rr, xi[u]);
+                        else self_ix(rr, xi[u]);
+                    }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (r + u < r1) {
-                        float x[NV];
-                        widen_term(xr[u], x);
-                        piece(x, c[u], xi[u]);
-                        step(s[u], x, c[u], xi[u]);
+                    for (int u = 0; u < U; ++u) {
+                        if (r + u < r1) {
+                            float x[NV];
+                            widen_term(xr[u], x);
+                            piece(x, c[u], xi[u]);
+                            step(s[u], x, c[u], xi[u]);
+                        }
                     }
                 }
+            } else {
+                // N rows from r, those past r1 (PAD) as above
+                auto batch = [&](auto n_tag, auto pad_tag) {
+                    constexpr int N = decltype(n_tag)::value;
+                    constexpr bool PAD = decltype(pad_tag)::value;
+                    int32_t s[N];
+                    Cnt c[N];
+                    RV xr[N][NT];
+                    uint32_t xi[N][NX];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) s[u] = (int32_t)idx[PAD ? min(r + u, r1 - 1) : r + u];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        load_term(PAD ? min(r + u, r1 - 1) : r + u, xr[u], c[u]);
+                        self_ix(r + u, xi[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        if (!PAD || r + u < r1) {
+                            float x[NV];
+                            widen_term(xr[u], x);
+                            step(s[u], x, c[u], xi[u]);
+                        }
+                    }
+                };
+                constexpr int UT = U > 4 ? 4 : 2;   // rows of a padded batch
+                for (; r + U <= r1; r += U) batch(std::integral_constant<int, U>{}, std::false_type{});
+                for (; r < r1; r += UT) batch(std::integral_constant<int, UT>{}, std::true_type{});
             }
         }
         // empty segments before this run (written after the row loop, so the first loads of

@@ -370,6 +370,50 @@ int ragged_vec(const Problem &p) {
     return p.F == 3 ? 3 : 4;
 }
 
+// Most rows per row group of 16-bit storage in 8-element vectors (`lanes` a row, 0: from the width).
+// Long runs amortise the block's scan; short ones keep the chip filled (two blocks for each of the
+// 256 CUs) and, where segments are about as long as the run, keep a block from holding too many
+// segments' ends at once. us at runs of 16 / 32 / 48 / 64 rows:
+// - segments of 500, bf16 sum: 40,000,000 rows of 48 columns 965, 805, 748, 737; 20,000,000 of 64 494,
+//   472, 424, 499; 2,000,000 of 32 32.3, 33.3, 28.9, 28.6; 10,000,000 of 128 562, 433, 441, 481;
+//   5,000,000 of 256 501, 434, 446, 456; 13,333,333 of 96 639, 547, 507, 488; 6,666,666 of 200 645, 573,
+//   540, 520. Rows of a power of two of columns put the row groups' runs a power of two apart in
+//   memory and want 48 or 32.
+// - segments of 16, max: 12,500,000 rows of 64 columns 315, 367, 336, 377; 16,666,666 of 48 347, 358,
+//   358, 374; 8,333,333 of 96 339, 323, 335, 353. Mean divides at every end: 1,500,007 fp16 rows of 47
+//   columns in segments of 9, 64.6 at 16, 69.8 at 32.
+// - up to 16 columns 16 rows (40,000,000 of 16 columns, segments of 500: 317, 335, 373, 343), but few
+//   rows in long segments want 32 (2,000,000: 23.8, 20.7, 23.3, 25.0).
+// - fewer than two blocks a CU, segments of 50: 300,000 rows of 64 columns 15.9, 19.5, 23.9, 28.6; of
+//   128 columns 26.8, 23.7, 27.2, 31.9.
+// - gathers below 2^21 edges (16 / 32 / 64 rows): 1,900,000 of 64 columns 52, 53, 53; of 128 98, 85, 86;
+//   1,000,000 of 256 104, 97, 85; 400,000 of 256 54, 41, 41; of 128 columns in segments of 7, 1,900,000
+//   117, 107, 109 but 1,200,007 68, 71, 70 (too few rounds of blocks).
+// - max with recipients, whose run is doubled below (32 / 48 / 64 rows): 10,000,000 rows of 64 columns
+//   305, 292, 304; 20,000,000 of 48 582, 539, 528; 300,000 of 128 32.0, 35.6, 42.5.
+int most_rows16(const Problem &p, int lanes) {
+    const int64_t vecs = ceil_div(p.F, 8), L = lanes != 0 ? std::min(lanes, 32) : std::min<int64_t>(32, pow2ceil(vecs));
+    const int64_t tiles = ceil_div(vecs, L);
+    auto mean_from = [&](int64_t len) { return p.nnz / len >= p.S; };
+    auto fills = [&](int64_t rows) { return p.nnz >= ceil_div(512 * (kBlock / L) * rows, tiles); };
+    if (p.gather) {
+        if (p.arg) return p.nnz < ((int64_t)1 << 21) ? 16 : 4096;
+        if (p.nnz >= ((int64_t)1 << 21)) return 4096;
+        if (p.F <= 64 || !fills(32)) return 16;
+        if (p.F <= 128 && !mean_from(32)) return fills(6 * 32) ? 32 : 16;
+        return fills(128) ? 128 : fills(64) ? 64 : 32;
+    }
+    if (p.arg) return p.F > 16 && fills(48) ? 24 : 16;
+    if (p.F <= 16) {
+        const bool few = p.nnz >= ((int64_t)1 << 20) && p.nnz < ((int64_t)1 << 22);
+        return p.F > 8 && few && mean_from(128) ? 32 : 16;
+    }
+    int rows;
+    if (p.F <= 64) rows = mean_from(32) ? 48 : p.F == 64 || (p.op == GEOT_OP_MEAN && p.F > 32) ? 16 : 32;
+    else rows = mean_from(32) && (p.F & (p.F - 1)) != 0 ? 64 : 32;
+    return fills(rows) ? rows : rows == 64 && fills(32) ? 32 : 16;
+}
+
 geot_status_t resolve(const Problem &p, const geot_kernel_choice_t &c, Resolved *r,
                       bool from_selector = false) {
     const int loads = GEOT_FLAG_NT_LOADS | GEOT_FLAG_CACHED_LOADS;
@@ -397,17 +441,8 @@ geot_status_t resolve(const Problem &p, const geot_kernel_choice_t &c, Resolved 
         const int v32 = c.vec != 0 ? std::min(c.vec, 4) : 4;
         V = 8;
         if (lanes != 0) lanes = std::max(1, lanes * v32 / V);
-        // ... up to 16 rows (24 above 64 columns, 32 from 17 to 32) of a segment reduction, whose
-        // blocks otherwise hold too many segments' ends at once: 16,777,216 bf16 rows of 64 columns
-        // in segments of about 16, max, 405 us at 16 rows, 417 at 24, 489 at 64; 4,000,000 of 128:
-        // 226, 204, 228; 300,000 of 64: 16.5, 18.4, 32.5; 8,000,000 of 16: 84, 90, 99 (32);
-        // 20,000,000 of 32: 276, 269, 271 (32). Gathers up to 16 edges below 2^21, where longer runs leave the chip idle (1,200,007
-        // edges of 47 columns 51 against 64 us at 32, 200,000 of 128: 19 against 23), while
-        // 10,000,000 edges of 128 take 446 at 16 and 413 at 32.
-        if (rows != 0) {
-            const int most = !p.gather ? (p.F > 64 ? 24 : p.F > 32 || p.F <= 16 ? 16 : 32) : (p.nnz < ((int64_t)1 << 21) ? 16 : 4096);
-            rows = std::min(most, rows * V / v32);
-        }
+        // ... up to what the shape takes
+        if (rows != 0) rows = std::min(most_rows16(p, lanes), rows * V / v32);
     }
     if (from_selector && p.arg && rows != 0) {
         // Carrying the recipients doubles what the block scan moves and holds registers (the

@@ -68,3 +68,32 @@ def test_column_tiles_by_the_size_of_x(nnz, F, x_rows):
     big = torch.zeros(200_000, F, device=DEV)
     big[:x_rows] = x
     compare(geot.gather_scatter_ws(big, col, w, row, R, "sum", ws).cpu().numpy(), ref, "sum", terms, "large X")
+
+
+@pytest.mark.parametrize("F,n,mean,rows", [(48, 900_000, 300, 48), (48, 900_000, 9, 32), (64, 900_000, 9, 16),
+                                           (96, 700_000, 300, 64), (128, 300_000, 300, 32), (48, 60_000, 300, 16)])
+def test_row_runs_follow_segment_length_and_grid(F, n, mean, rows):
+    """Long segments take long row runs where the grid stays full; at most `rows` otherwise. Same sums."""
+    p = random_problem(F + mean, n, n // mean, F, "poisson", "normal", 0.0)
+    s, wide = stored(p["src"], torch.bfloat16, 0)
+    i = torch.from_numpy(p["index"]).to(DEV)
+    say(f"row runs F={F} n={n} mean={mean}")
+    ref, terms = oracle_segment(wide, p["index"], n // mean, "sum")
+    compare(geot.segment_reduce(s, i, n // mean, "sum").cpu().numpy(), ref, "sum", terms, f"F={F}")
+    got = geot.last_choice()["rows"]
+    assert got <= rows and (rows < 32 or got >= 32), got
+
+
+@pytest.mark.parametrize("F,n,rows", [(64, 1_000_000, 16), (128, 1_000_000, 32), (256, 400_000, 32), (128, 60_000, 16)])
+def test_row_runs_of_gathers(F, n, rows):
+    """Gathers of more than 64 columns whose grid stays full keep runs of 32 edges or more."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    S, nx = n // 100, n // 8
+    row = torch.sort(torch.randint(0, S, (n,), device=DEV, generator=g)).values
+    col = torch.randint(0, nx, (n,), device=DEV, generator=g)
+    x = torch.randint(-4, 5, (nx, F), device=DEV, generator=g).to(torch.bfloat16)   # integers: exact sums
+    say(f"gather row runs F={F} n={n}")
+    got = geot.gather_scatter(x, col, None, row, S)
+    used = geot.last_choice()["rows"]
+    assert torch.equal(got, torch.zeros(S, F, device=DEV).index_add_(0, row, x.float()[col]))
+    assert used >= 32 if rows >= 32 else used <= rows, used

@@ -892,9 +892,9 @@ __global__ __launch_bounds__(256) void gs_bwd_max_arg_run_kernel(const typename 
 // that span runs cost more than the balance gives (whole gradient w.r.t. X, us at runs of 32 / 64 /
 // 128 / 256 / 512: 400,000 edges of 64 columns 131 / 136 / 158 / 204 / 298; 1,000,000 of 100: 295 /
 // 303 / 288 / 316 / 421; 8,000,000 of 64: 751 / 732 / 728 / 768 / 703; the SpMM graph 5,794 / 5,482
-// / 5,298 / 5,200 / 5,217).
+// / 5,298 / 5,200 / 5,217). At most 256: a run is one chain of sums, and longer ones round further off.
 int pull_run(int64_t n) {
-    return n >= ((int64_t)1 << 24) ? 512 : n >= ((int64_t)1 << 20) ? 128 : 32;
+    return n >= ((int64_t)1 << 24) ? 256 : n >= ((int64_t)1 << 20) ? 128 : 32;
 }
 
 template <int V, bool COOP>

@@ -145,7 +145,8 @@ __global__ __launch_bounds__(kJoinBlock) void ep_join_kernel(const EpArgs a, con
     }
     __syncthreads();
     // this thread's share of the run that starts at block `cl`: the lo partials of blocks k0, k0 + by,
-    // ... (kU at a time, at most `trips` times); returns whether the run may go on behind them
+    // ... (kU at a time, at most `trips` times); returns whether the run may go on behind them. Each turn's
+    // partials are combined by themselves first: no chain of sums is longer than a turn's or the turns
     auto walk = [&](auto ut, int32_t seg, int64_t k0, int64_t by, int trips, int j, bool lane, float *v, uint32_t *vi, int64_t &n) {
         constexpr int kU = decltype(ut)::value;
         bool more = true;
@@ -160,14 +161,18 @@ __global__ __launch_bounds__(kJoinBlock) void ep_join_kernel(const EpArgs a, con
                 cnt[u] = k < chunks ? count_of(2 * kk) : 0;
                 load(2 * kk, j, lane, x[u], xi[u]);
             }
+            more = cnt[0] > 0 && id[0] == seg;
+            if (!more) break;
+            n += cnt[0];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {   // the run is contiguous: past its end nothing matches
+            for (int u = 1; u < kU; ++u) {   // the run is contiguous: past its end nothing matches
                 more = more && cnt[u] > 0 && id[u] == seg;
                 if (more) {
-                    take(v, vi, x[u], xi[u]);
+                    take(x[0], xi[0], x[u], xi[u]);
                     n += cnt[u];
                 }
             }
+            take(v, vi, x[0], xi[0]);
         }
         return more && k0 < chunks;
     };

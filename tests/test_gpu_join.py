@@ -65,3 +65,43 @@ def test_join_special_values():
     want = np.full((S, F), NONE, dtype=np.uint64)
     np.minimum.at(want, index, np.where(src == ref[index], np.arange(index.size, dtype=np.uint64)[:, None], np.uint64(NONE)))
     assert np.array_equal(arg.cpu().numpy().view(np.uint32), want.astype(np.uint32))
+
+
+@pytest.mark.parametrize("F", [1, 4])
+def test_join_by_the_block(F):
+    """A segment over 1,500 blocks of 4 rows, more than a wave's turns reach over at rows of one vector
+    (1,024 partials): the thread block's walk, with 512 groups."""
+    rng = np.random.default_rng(F)
+    S = 900
+    n = rng.integers(0, 9, S)
+    n[S // 2] = 6000
+    index = np.repeat(np.arange(S), n).astype(np.int64)
+    assert index.size <= S * 16 and index.size // 4 > 1024     # few enough rows a segment for the join
+    src = rng.integers(-6, 7, (index.size, F)).astype(np.float32)
+    s, i = torch.from_numpy(src).to(DEV), torch.from_numpy(index).to(DEV)
+    choice = dict(family="ep", rows=1, lanes=64)
+    say(f"join by the block F={F}")
+    for op in ("sum", "mean", "max"):
+        ref, terms = oracle_segment(src, index, S, op)
+        compare(geot.segment_reduce(s, i, S, op, choice=choice).cpu().numpy(), ref, op, terms, op)
+    out, arg = geot.segment_reduce_max_arg(s, i, S, choice=choice)
+    ref = oracle.segment_reduce(src, index, S, "max")
+    compare(out.cpu().numpy(), ref, "max", what="max with recipients")
+    want = np.full((S, F), NONE, dtype=np.uint64)
+    np.minimum.at(want, index, np.where(src == ref[index], np.arange(index.size, dtype=np.uint64)[:, None], np.uint64(NONE)))
+    assert np.array_equal(arg.cpu().numpy().view(np.uint32), want.astype(np.uint32))
+
+
+def test_join_sums_in_short_chains():
+    """2,400 partials of 1 + 2^-16 in one segment, 300 for each of the block's 8 groups: in one chain every
+    term past the 256th would lose its 2^-16 (2e-6 of the sum). Sums of 16 and sums of those are exact; what
+    remains are the last three roundings, of 2^-24 each."""
+    S, F, blocks = 700, 260, 2400
+    index = torch.full((4 * blocks,), 5, device=DEV)
+    src = torch.full((4 * blocks, F), 0.25 * (1 + 2.0 ** -16), device=DEV)
+    assert 4 * blocks <= S * 16 and blocks * F * 4 <= 5 << 19
+    say("join, short chains")
+    out = geot.segment_reduce(src, index, S, "sum", choice=dict(family="ep", rows=1, lanes=64))
+    want = blocks * (1 + 2.0 ** -16)
+    assert float((out[5].double() - want).abs().max()) <= 3 * 2.0 ** -24 * want
+    assert int((out != 0).any(1).sum()) == 1

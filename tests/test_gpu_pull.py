@@ -71,3 +71,17 @@ def test_pull_skips_columns_out_of_range(n):
     wrong[bad] = rng.choice([-1, nx, nx + 5, -(1 << 40)], int(bad.sum()))
     got, _ = geot.gather_scatter_backward_max_arg(up(X), up(wrong), None, up(row), up(g), up(a))
     assert torch.equal(got, want)
+
+
+def test_pull_sums_in_short_chains():
+    """Columns of 512 terms of 1 + 2^-16 in a long list: runs are one chain of at most 256, which is exact, as
+    is the sum of two; past the 256th term a chain would lose the 2^-16 of every one."""
+    n = (1 << 24) + 512
+    row = torch.arange(n, device=DEV)
+    col = row // 512
+    nx = n // 512
+    say("pull, short chains")
+    g = torch.full((n, 1), 1 + 2.0 ** -16, device=DEV)
+    x = torch.zeros(nx, 1, device=DEV)
+    gx, _ = geot.gather_scatter_backward_max_arg(x, col, None, row, g, row.int()[:, None].contiguous(), need_weight=False)
+    assert torch.all(gx == 512 * (1 + 2.0 ** -16))

@@ -826,7 +826,48 @@ geot_status_t run_sp_kernels(const Problem &p, const Resolved &r, int64_t *off, 
     return GEOT_SUCCESS;
 }
 
-constexpr int64_t kUntileBytes = (int64_t)64 << 20;
+// A gather's leaf with column tiles in sequence: kept, or undone for whole rows. Tiles read the ids once
+// each and leave a smaller slab of X to the caches; the leaves know neither X's type nor its rows. us for
+// the leaf / for whole rows, fp32 with uniform columns unless said:
+// - 16-bit X: the slab saves nothing (SpMM shape, bf16: 2,920 / 2,830).
+// - few elements (nnz * F below 2^26): 200,000 edges of 64 columns (X of 32 MB, segments of 8) 33 / 17, of
+//   100 37 / 26, of 256 (60 MB) 44 / 42; 1,000,000 of 64 (32 MB) 55 / 46.
+// - F not a multiple of the tile, the tiles leaving as many lanes idle as whole rows: 4,000,000 edges
+//   (60 MB, segments of 60) of 100 columns 517 / 296, of 200 670 / 498. Where they leave fewer (160 columns
+//   in three tiles of 64) they stay up to an X of 64 MB: X of 4 / 16 / 60 / 240 MB 276 / 331, 297 / 347,
+//   381 / 372, 417 / 389.
+// - else by X. Whole rows where it fits an XCD's 4 MB of L2 (1,000,000 edges of 256 columns, segments of
+//   8, 60, 400: 145 / 109, 97 / 101, 99 / 100) and, while it fits the 256 MB MALL, for rows of 64 columns
+//   (4,000,000 edges, 4, 32, 240 MB: 100 / 92, 175 / 150, 207 / 165) and for up to 128 where four tiles
+//   leave a slab of over 14 MB (4,000,000, 60 and 240 MB: 313 / 297, 370 / 318). Else the tiles (whole rows
+//   are slower at 20,000,000 edges of 128 columns, 16, 32 and 51 MB: 1,046 / 1,137, 1,193 / 1,302,
+//   1,300 / 1,376; 4,000,000 of 256, 16 and 32 MB: 333 / 452, 421 / 524).
+// The leaf's run of rows goes with its narrower groups; whole rows take 16 to 64 (or the leaf's, if more),
+// as long as two blocks a CU remain, up to 32 of few elements and of an X over 32 MB up to 128 columns
+// (1,200,007 edges of 100 columns 105 at 32, 109 at 64).
+void settle_tiles(const Problem &p, geot_kernel_choice_t *c) {
+    if (!p.gather || (c->flags & GEOT_FLAG_TILE_MAJOR) == 0) return;
+    if (p.esize() == 2) {
+        untile(c);
+        c->rows = std::min(c->rows, p.F > 64 ? 32 : 16);
+        return;
+    }
+    const int64_t mb = (int64_t)1 << 20, tile = 4 * c->lanes, tiles = ceil_div(p.F, tile);
+    int L, NT;
+    auto_lanes(p.F, 4, &L, &NT);
+    const int64_t whole = (int64_t)4 * L * NT;
+    auto x_below = [&](int64_t bytes) { return p.num_x_rows <= bytes / 4 / p.F; };
+    const bool few = p.nnz < ceil_div((int64_t)1 << 26, p.F);
+    bool undo;
+    if (few) undo = true;
+    else if (p.F % tile != 0) undo = tiles * tile >= ceil_div(p.F, whole) * whole || !x_below(64 * mb);
+    else undo = x_below(4 * mb) || (x_below(256 * mb) && (p.F <= 64 || (p.F <= 128 && tiles >= 4 && !x_below(56 * mb))));
+    if (!undo) return;
+    const int most = few || (p.F <= 128 && !x_below(32 * mb)) ? 32 : std::max(64, c->rows);
+    untile(c);
+    c->rows = 16;
+    while (c->rows < most && p.nnz / (512 * (kBlock / L)) >= 2 * c->rows) c->rows *= 2;
+}
 
 // The kernel choice of a call: the forced one, else the selector's for the problem.
 geot_kernel_choice_t choose(const Problem &p, const geot_kernel_choice_t *forced) {
@@ -834,17 +875,7 @@ geot_kernel_choice_t choose(const Problem &p, const geot_kernel_choice_t *forced
     geot_kernel_choice_t c;
     select_raw(p.nnz, p.S, p.F, p.op, p.gather ? (p.w ? 1 : 2) : 0, nullptr, &c);
     if ((p.typed() || p.arg) && c.family == GEOT_FAMILY_SP) c = geot_kernel_choice_t{GEOT_FAMILY_EP, 0, 0, 0, 0, 0};
-    // Column tiles in sequence read the ids once per tile for a smaller slab of X. The leaves know
-    // neither X's type nor its rows: the slab saves nothing where X is 16-bit (SpMM shape, bf16:
-    // 2.92 ms with two tiles, 2.83 without) or fits the caches (X of 64 MB or less: 200,000 edges
-    // of 64 columns 32 against 16 us, of 128 26 against 21), or where the last tile is mostly
-    // empty (1,200,007 edges of 100 columns, 4 tiles of 32: 161 against 103 us). The run of rows of
-    // such a leaf goes with its narrower groups; whole rows take 32 edges, 16 up to 64 columns.
-    if ((c.flags & GEOT_FLAG_TILE_MAJOR) &&
-        (p.esize() == 2 || p.num_x_rows <= kUntileBytes / 4 / p.F || p.F % (4 * c.lanes) != 0)) {
-        untile(&c);
-        if (c.rows > (p.F > 64 ? 32 : 16) || p.esize() != 2) c.rows = p.F > 64 ? 32 : 16;
-    }
+    settle_tiles(p, &c);
     return c;
 }
 
@@ -888,7 +919,7 @@ geot_status_t reduce(const Problem &p, hipStream_t st, const geot_kernel_choice_
 
 // Workspace a call of this shape needs, whatever the alignment of its arrays and the rows of X: the
 // largest need over the vector widths that F and the pointers may allow (the pointers decide the
-// width, and the width the partials' count) and over the choices a small and a large X get.
+// width, and the width the partials' count) and over the choices that a small, a middle and a large X get.
 geot_status_t workspace_size(Problem p, const geot_kernel_choice_t *forced, size_t *bytes) {
     t_detail.clear();
     if (!bytes) return fail(GEOT_ERROR_INVALID_VALUE, "bytes is NULL");
@@ -905,7 +936,7 @@ geot_status_t workspace_size(Problem p, const geot_kernel_choice_t *forced, size
     for (uintptr_t align : {(uintptr_t)256, (uintptr_t)8, (uintptr_t)4}) {
         p.src = (const void *)align;
         p.out = (float *)align;
-        for (int64_t x_rows : {(int64_t)1, (int64_t)1 << 60}) {
+        for (int64_t x_rows : {(int64_t)1, ((int64_t)64 << 20) / 4 / p.F, (int64_t)1 << 60}) {   // (see settle_tiles)
             p.num_x_rows = x_rows;
             Resolved r;
             geot_status_t s = resolve(p, choose(p, forced), &r, forced == nullptr);

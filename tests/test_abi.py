@@ -11,6 +11,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import paper_2404_03019_amd as geot
 from paper_2404_03019_amd.geot import KernelChoice, lib
@@ -270,3 +271,24 @@ def test_recipient_calls_check_on_the_host():
                                                   None, None) == INVALID
     # no rows: nothing to do, no device work
     assert L.geot_segment_reduce_backward_max_arg(g, idx, I64, 0, 10, 4, arg, gs, F32, None) == SUCCESS
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the calls that pass the check go on to launch")
+@pytest.mark.parametrize("F", [24, 47, 64, 96, 100, 128, 160, 200, 256, 300])
+def test_workspace_covers_every_number_of_x_rows(F):
+    """The size query does not know X; the kernel choice depends on its rows. With a workspace of the queried
+    size no call is refused for it (without a device it ends at the first launch instead)."""
+    L = lib()
+    refused = []
+    for nnz in (30_000, 200_000, 700_000, 1_200_007, 5_000_000, 40_000_000):
+        for mean in (3, 20, 90, 500, 3000):
+            R = max(1, nnz // mean)
+            for weight in (FAKE, None):
+                need = geot.workspace_size(nnz, R, F, "sum", gather=True, weighted=weight is not None)
+                for mb in (0.5, 3, 5, 16, 31, 33, 50, 57, 65, 120, 250, 260, 1200):
+                    nx = max(1, int(mb * (1 << 20) / 4 / F))
+                    st = L.geot_gather_scatter_ws(FAKE, nx, FAKE << 1, weight and FAKE << 2, FAKE << 3, nnz, R, F, 0, FAKE << 8,
+                                                  FAKE << 9, need, None, None)
+                    if st == INVALID:
+                        refused.append((nnz, mean, weight is not None, mb, _detail()))
+    assert not refused, refused[:3]

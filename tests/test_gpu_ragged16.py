@@ -70,6 +70,25 @@ def test_column_tiles_by_the_size_of_x(nnz, F, x_rows):
     compare(geot.gather_scatter_ws(big, col, w, row, R, "sum", ws).cpu().numpy(), ref, "sum", terms, "large X")
 
 
+@pytest.mark.parametrize("nnz,F,x_rows,tiled", [(1_200_000, 128, 32_000, True), (600_000, 256, 50_000, True),
+                                                (900_000, 160, 50_000, True), (1_200_000, 128, 7_000, False),
+                                                (300_000, 128, 100_000, False), (900_000, 100, 100_000, False)])
+def test_column_tiles_kept_where_their_slab_fits(nnz, F, x_rows, tiled):
+    """X of 16 to 51 MB in tiles whose slabs the L2s hold keeps them; an X that fits one L2, few elements and
+    tiles of idle lanes take whole rows. Same sums."""
+    g = torch.Generator(device=DEV).manual_seed(nnz)
+    R = nnz // 60
+    row = torch.sort(torch.randint(0, R, (nnz,), device=DEV, generator=g)).values
+    col = torch.randint(0, x_rows, (nnz,), device=DEV, generator=g)
+    x = torch.randint(-4, 5, (x_rows, F), device=DEV, generator=g).float()   # integers: exact sums
+    w = torch.randint(1, 3, (nnz,), device=DEV, generator=g).float()
+    say(f"tiles kept nnz={nnz} F={F} X rows={x_rows}")
+    got = geot.gather_scatter(x, col, w, row, R)
+    used = geot.last_choice()["flags"] & 4
+    assert torch.equal(got, torch.zeros(R, F, device=DEV).index_add_(0, row, x[col] * w[:, None]))
+    assert bool(used) == tiled, geot.last_choice()
+
+
 @pytest.mark.parametrize("F,n,mean,rows", [(48, 900_000, 300, 48), (48, 900_000, 9, 32), (64, 900_000, 9, 16),
                                            (96, 700_000, 300, 64), (128, 300_000, 300, 32), (48, 60_000, 300, 16)])
 def test_row_runs_follow_segment_length_and_grid(F, n, mean, rows):

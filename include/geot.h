@@ -461,9 +461,16 @@ geot_status_t geot_transpose_edges(const int64_t *col, int64_t num_x_rows, const
  *           longest segment join the features, and the segment-parallel
  *           family is never chosen when the longest segment exceeds 256x the
  *           mean length
- * Writes a fully specified choice to *out.                                  */
+ * Writes a fully specified choice to *out. geot_select does not know X: for a
+ * gather it returns the tree's choice with its column tiles as they are. A call
+ * without a choice also looks at the rows of X (tiles in sequence do not pay
+ * where X is small, for instance) and may run whole rows instead;
+ * geot_select_gather takes them and returns what such a call runs (fp32, int64
+ * ids, aligned arrays; with statistics, what it would run if it had them).  */
 geot_status_t geot_select(int64_t nnz, int64_t num_segments, int64_t F, geot_op_t op, int32_t gather,
                           const geot_index_stats_t *stats, geot_kernel_choice_t *out);
+geot_status_t geot_select_gather(int64_t nnz, int64_t num_x_rows, int64_t num_rows, int64_t F, geot_op_t op,
+                                 int32_t weighted, const geot_index_stats_t *stats, geot_kernel_choice_t *out);
 
 /* Segment-length statistics of a sorted index (one pass over the index on
  * the device). Synchronizes `stream`; writes the host struct *host_out.

@@ -1565,8 +1565,9 @@ geot_status_t geot_transpose_edges(const int64_t *col, int64_t num_x_rows, const
     return scratch_free(p_free, st);
 }
 
-geot_status_t geot_select(int64_t nnz, int64_t num_segments, int64_t F, geot_op_t op, int32_t gather,
-                          const geot_index_stats_t *stats, geot_kernel_choice_t *out) {
+// x_rows < 0: not known, and the leaf's column tiles stay as they are
+static geot_status_t select_resolved(int64_t nnz, int64_t x_rows, int64_t num_segments, int64_t F, geot_op_t op,
+                                     int32_t gather, const geot_index_stats_t *stats, geot_kernel_choice_t *out) {
     t_detail.clear();
     if (!out) return fail(GEOT_ERROR_INVALID_VALUE, "out is NULL");
     if (op != GEOT_OP_SUM && op != GEOT_OP_MEAN && op != GEOT_OP_MAX)
@@ -1579,13 +1580,28 @@ geot_status_t geot_select(int64_t nnz, int64_t num_segments, int64_t F, geot_op_
         return GEOT_SUCCESS;
     }
     // resolve against 256-byte aligned pointers (what device allocators return)
-    Problem p{gather != 0, (const float *)(uintptr_t)256, 0, nullptr, nullptr, nullptr,
+    Problem p{gather != 0, (const float *)(uintptr_t)256, x_rows, nullptr, nullptr, nullptr,
               nnz, num_segments, F, op, (float *)(uintptr_t)256};
+    if (x_rows >= 0) settle_tiles(p, &c);
     Resolved r;
     geot_status_t s = resolve(p, c, &r, true);
     if (s != GEOT_SUCCESS) return s;
     *out = to_choice(r);
     return GEOT_SUCCESS;
+}
+
+geot_status_t geot_select(int64_t nnz, int64_t num_segments, int64_t F, geot_op_t op, int32_t gather,
+                          const geot_index_stats_t *stats, geot_kernel_choice_t *out) {
+    return select_resolved(nnz, -1, num_segments, F, op, gather, stats, out);
+}
+
+geot_status_t geot_select_gather(int64_t nnz, int64_t num_x_rows, int64_t num_rows, int64_t F, geot_op_t op,
+                                 int32_t weighted, const geot_index_stats_t *stats, geot_kernel_choice_t *out) {
+    if (num_x_rows < 0) {
+        t_detail.clear();
+        return fail(GEOT_ERROR_INVALID_VALUE, "negative size");
+    }
+    return select_resolved(nnz, num_x_rows, num_rows, F, op, weighted ? 1 : 2, stats, out);
 }
 
 geot_status_t geot_index_stats(const int64_t *sorted_index, int64_t nnz, int64_t num_segments,

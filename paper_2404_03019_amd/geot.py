@@ -68,6 +68,7 @@ def lib() -> ctypes.CDLL:
     L.geot_gather_scatter_typed.argtypes = [p, ctypes.c_int, i64, p, p, p, ctypes.c_int, i64, i64, i64,
                                             ctypes.c_int, p, p, pc]
     L.geot_select.argtypes = [i64, i64, i64, ctypes.c_int, i32, ctypes.POINTER(IndexStats), pc]
+    L.geot_select_gather.argtypes = [i64, i64, i64, i64, ctypes.c_int, i32, ctypes.POINTER(IndexStats), pc]
     L.geot_index_stats.argtypes = [p, i64, i64, ctypes.POINTER(IndexStats), p]
     L.geot_check_index.argtypes = [p, i64, i64, p, i64, p]
     L.geot_segment_reduce_backward.argtypes = [p, p, i64, i64, i64, ctypes.c_int, p, p, p, p]
@@ -102,7 +103,7 @@ def lib() -> ctypes.CDLL:
     L.geot_last_error_detail.restype = ctypes.c_char_p
     L.geot_version.restype = i32
     for name in ("geot_segment_reduce", "geot_segment_reduce_with", "geot_gather_scatter",
-                 "geot_gather_scatter_with", "geot_select", "geot_index_stats", "geot_check_index",
+                 "geot_gather_scatter_with", "geot_select", "geot_select_gather", "geot_index_stats", "geot_check_index",
                  "geot_last_choice", "geot_profile_begin", "geot_profile_end", "geot_release_scratch",
                  "geot_segment_reduce_backward", "geot_gather_scatter_backward",
                  "geot_segment_reduce_workspace_size", "geot_gather_scatter_workspace_size",
@@ -193,13 +194,13 @@ DTYPES = {torch.float32: 0, torch.bfloat16: 1, torch.float16: 2}
 INDEX_TYPES = {torch.int64: 0, torch.int32: 1}
 
 
-def _stats_choice(choice, stats, nnz, S, F, reduce, gather, weighted, plain):
+def _stats_choice(choice, stats, nnz, S, F, reduce, gather, weighted, plain, x_rows=None):
     """The selector's choice with the index statistics `stats` (geot_index_stats of the same
     index, computed once by the caller, e.g. per static graph) when no choice is forced; the
     segment-parallel family it may pick takes fp32 data with int64 ids only (`plain`)."""
     if choice is not None or stats is None or not plain:
         return choice
-    return select(nnz, S, F, reduce, gather=gather, stats=stats, weighted=weighted)
+    return select(nnz, S, F, reduce, gather=gather, stats=stats, weighted=weighted, x_rows=x_rows)
 
 
 def segment_reduce(src: torch.Tensor, index: torch.Tensor, num_segments: int, reduce: str = "sum",
@@ -260,7 +261,7 @@ def gather_scatter(x: torch.Tensor, col: torch.Tensor, weight: torch.Tensor | No
     if out is None:
         out = torch.empty((R, F), dtype=torch.float32, device=x.device)
     plain = x.dtype == torch.float32 and col.dtype == torch.int64
-    c = _choice(_stats_choice(choice, stats, row.numel(), R, F, reduce, True, weight is not None, plain))
+    c = _choice(_stats_choice(choice, stats, row.numel(), R, F, reduce, True, weight is not None, plain, x.shape[0]))
     wp = weight.data_ptr() if weight is not None else None
     cp = ctypes.byref(c) if c is not None else None
     with _OnDevice(x.device):
@@ -628,14 +629,19 @@ def check_index(index: torch.Tensor, num_segments: int, col: torch.Tensor | None
 
 
 def select(nnz: int, num_segments: int, F: int, reduce: str = "sum", gather: bool = False,
-           stats: dict | None = None, weighted: bool = True) -> dict:
+           stats: dict | None = None, weighted: bool = True, x_rows: int | None = None) -> dict:
     """The selector's kernel choice for a shape (geot_select; host only). `weighted`
-    says whether a fused gather has edge weights."""
+    says whether a fused gather has edge weights; with `x_rows`, the rows of its X, the choice
+    is the one that a call of this shape makes (geot_select_gather)."""
     c = KernelChoice()
     sp = None
     if stats is not None:
         s = IndexStats(**{k: stats[k] for k, _ in IndexStats._fields_})
         sp = ctypes.byref(s)
+    if gather and x_rows is not None:
+        _raise(lib().geot_select_gather(int(nnz), int(x_rows), int(num_segments), int(F), OPS[reduce],
+                                        1 if weighted else 0, sp, ctypes.byref(c)))
+        return c.as_dict()
     g = 0 if not gather else (1 if weighted else 2)
     _raise(lib().geot_select(int(nnz), int(num_segments), int(F), OPS[reduce], g, sp, ctypes.byref(c)))
     return c.as_dict()

@@ -292,3 +292,25 @@ def test_workspace_covers_every_number_of_x_rows(F):
                     if st == INVALID:
                         refused.append((nnz, mean, weight is not None, mb, _detail()))
     assert not refused, refused[:3]
+
+
+def _stats(nnz, S, spread=0.3):
+    mean = nnz / S
+    return dict(nnz=nnz, num_segments=S, num_empty=0, max_len=int(4 * mean) + 1, sum_len_sq=0, mean_len=mean,
+                var_len=(spread * mean) ** 2)
+
+
+@pytest.mark.parametrize("nnz,R,F,x_rows", [(200_000, 20_000, 64, 20_000), (1_200_007, 170_003, 100, 170_003),
+                                            (4_000_000, 500_000, 100, 500_000), (4_000_000, 300_000, 200, 300_000)])
+def test_statistics_do_not_bring_back_column_tiles(nnz, R, F, x_rows):
+    """Where a call without statistics runs whole rows, so does one with them (such as every gather over a kept
+    graph); geot_select, which does not know X, still returns the tree's tiles."""
+    for spread in (0.1, 1.0, 3.0):
+        c = geot.select(nnz, R, F, gather=True, stats=_stats(nnz, R, spread), x_rows=x_rows)
+        assert not c["flags"] & 4, c
+    assert not geot.select(nnz, R, F, gather=True, x_rows=x_rows)["flags"] & 4
+    big = geot.select(61_859_140, 2_449_029, 128, gather=True, x_rows=2_449_029)
+    assert big == geot.select(61_859_140, 2_449_029, 128, gather=True)     # the SpMM graph keeps its two tiles
+    assert big["flags"] & 4
+    bad = KernelChoice()
+    assert lib().geot_select_gather(10, -1, 4, 4, 0, 1, None, ctypes.byref(bad)) == INVALID

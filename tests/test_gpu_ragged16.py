@@ -87,6 +87,11 @@ def test_column_tiles_kept_where_their_slab_fits(nnz, F, x_rows, tiled):
     used = geot.last_choice()["flags"] & 4
     assert torch.equal(got, torch.zeros(R, F, device=DEV).index_add_(0, row, x[col] * w[:, None]))
     assert bool(used) == tiled, geot.last_choice()
+    plain = geot.last_choice()
+    assert plain == geot.select(nnz, R, F, gather=True, x_rows=x_rows)     # what geot_select_gather says
+    with_stats = geot.gather_scatter(x, col, w, row, R, stats=geot.index_stats(row, R))
+    assert torch.equal(got, with_stats)
+    assert tiled or not geot.last_choice()["flags"] & 4
 
 
 @pytest.mark.parametrize("F,n,mean,rows", [(48, 900_000, 300, 48), (48, 900_000, 9, 32), (64, 900_000, 9, 16),

@@ -73,12 +73,16 @@ class Graph:
     (Section III-C: variance as a feature); they are refreshed when the ids are updated
     in place."""
 
+    # the gather over a transposed list that a few destinations hold most edges of, from 2^25 edges
+    TRANSPOSED_GATHER = dict(family="ep", rows=256)
+
     def __init__(self, col, row, num_nodes: int, weight=None, num_src: int | None = None):
         self.col, self.row, self.weight = col, row, weight
         self.num_nodes = int(num_nodes)
         self.num_src = int(num_src if num_src is not None else num_nodes)
         self._transposed = {}
         self._stats = None
+        self.gather_choice = None   # a kernel choice for that gather, where the program wants its own
 
     def stats(self):
         """geot_index_stats of the destination ids (kept until the ids change in place)."""
@@ -89,21 +93,37 @@ class Graph:
 
     def transposed_choice(self, F: int):
         """Kernel choice for the gather of F columns over the transposed list (whole rows: its gathered
-        rows are the destinations', which repeat as often as their edge counts).
+        rows are the destinations', which repeat as often as their edge counts); None: the library's.
 
-        Where a few destinations hold most edges (lengths spread over 8 times their mean) the rows come
-        from cache and long runs per row group pay for the block's scan; otherwise they come from
-        memory and short runs keep more blocks in flight. MI355X, 128 columns: 61,859,140 edges,
-        power-law rows, 2.96 ms at 256 rows, 3.02 at 128, 3.80 at 16; 10,000,000 edges, lognormal rows, 0.80 ms
-        at 256, 0.74 at 16. Up to 16 columns 8 rows are best either way (20,000,000 edges: 237 and
-        395 us against 396 and 601 at 256)."""
+        Rows that come from cache, because there are few of them or because a few destinations hold most
+        edges (lengths spread over 8 times their mean), take long runs per row group, which pay for the
+        block's scan, as long as two blocks a CU remain; rows that come from memory take short runs, which
+        keep more blocks in flight. MI355X, us at 16 / 32 / 64 / 128 rows per group: 2,000,000 edges of 64
+        columns into 33,333 destinations 63, 57, 53, 52; power law, 4,000,000 of 128 into 571,428 292, 259,
+        247, 237. From memory: 2,000,000 of 128 into 285,714 (146 MB) 171, 178, 175, 175; 16,000,000 of 32
+        into 266,666 (34 MB) 280, 294, 311, 322; wider rows the library's choice (8,000,000 of 200 into
+        1,142,857 1,152, 1,213 at 16). 61,859,140 edges, power-law rows, 128 columns: 2.96 ms at 256, 3.02
+        at 128, 3.80 at 16. From 9 to 16 columns 8 rows are best (4,000,000 of 16, power law: 53, 59 at 16,
+        66 by the library), below them the library's choice (of 8: 50, 56 at 8 rows). Below 2^20 edges the
+        library's choice (300,000 of 200, power law: 41, 50 at the longest run that fills the chip).
+        `gather_choice`, where set, comes first."""
         n = self.row.numel()
+        if self.gather_choice is not None:
+            return self.gather_choice
         if F <= 16:
-            rows = 8
-        elif n >= (1 << 21) and self._heavy():
-            rows = 256 if n >= (1 << 25) else 128
-        else:
-            rows = 16
+            return dict(family="ep", rows=8) if F > 8 and n >= (1 << 19) else None
+        if n < (1 << 20):
+            return None
+        cached = self.num_nodes * F * 4 <= ((32 << 20) if F <= 64 else (64 << 20))
+        if not cached and not self._heavy():
+            return dict(family="ep", rows=16) if F <= 128 else None
+        if n >= (1 << 25) and not cached:
+            return self.TRANSPOSED_GATHER
+        lanes = min(64, 1 << (-(-F // 4) - 1).bit_length())
+        tiles = -(-F // (4 * lanes))
+        rows = 16
+        while rows < 128 and n * tiles >= 512 * (256 // lanes) * 2 * rows:
+            rows *= 2
         return dict(family="ep", rows=rows)
 
     def _heavy(self) -> bool:

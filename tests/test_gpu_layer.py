@@ -13,6 +13,7 @@ import pytest
 import torch
 
 import paper_2404_03019_amd.autograd as ga
+from gpu_util import say
 from workloads import random_gather_problem
 
 pytestmark = pytest.mark.gpu
@@ -141,3 +142,24 @@ def test_gin_training_step(cached):
     for a, b in zip(m, ref):
         for (name, pa), pb in zip(a.named_parameters(), b.parameters()):
             close(pa.grad, pb.grad, (name, cached))
+
+
+@pytest.mark.parametrize("heavy,R", [(False, 300_000), (True, 300_000), (False, 30_000)])
+def test_gradient_over_long_kept_lists(heavy, R):
+    """The gather over a long transposed list takes short row runs, or long ones where its rows come from
+    cache: few destinations, or few that hold most edges. Small integers: the sums are exact in any order."""
+    n, nx, F = (1 << 22) + 77, 40_000, 40
+    g = torch.Generator(device=DEV).manual_seed(3)
+    w = torch.ones(R, device=DEV, dtype=torch.float64)
+    if heavy:
+        w[::5000] = 4 * R
+    row = torch.sort(torch.multinomial(w, n, replacement=True, generator=g)).values
+    col = torch.randint(0, nx, (n,), device=DEV, generator=g)
+    x = torch.randint(-3, 4, (nx, F), device=DEV, generator=g).float().requires_grad_()
+    go = torch.randint(-1, 2, (R, F), device=DEV, generator=g).float()
+    graph = ga.Graph(col, row, R, None, nx)
+    say(f"long kept list heavy={heavy} R={R}")
+    out = ga.gather_scatter(x, col, None, row, R, "sum", graph)
+    (gx,) = torch.autograd.grad(out, (x,), go)
+    assert graph.transposed_choice(F)["rows"] == (128 if heavy or R == 30_000 else 16)
+    assert torch.equal(gx, torch.zeros(nx, F, device=DEV).index_add_(0, col, go[row]))

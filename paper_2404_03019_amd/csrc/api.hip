@@ -626,8 +626,8 @@ int64_t piece_rows_k(int64_t n, int64_t G) {
 
 // blocks that write the gap list, as a pass of their own or riding on the final partial level (or join)
 constexpr int kFoldedGapBlocks = 1024;
-// segment gradients over ids of more bytes than this take the offsets pass first (below, the ids
-// stay in the 256 MB MALL from the pass before, or from the offsets pass of the mean)
+// segment gradients over ids, or gradient rows, of more bytes than this take the offsets pass first (below,
+// the ids stay in the 256 MB MALL from the pass before, or from the offsets pass of the mean)
 constexpr size_t kBcastOffsetsMinBytes = (size_t)200 << 20;
 
 // Shape of the passes over fp32 partials: 8-element vectors (16-bit storage)
@@ -1146,9 +1146,15 @@ static geot_status_t seg_backward(const float *grad_out, const void *sorted_inde
     // 20,000,000 rows (160 MB) in 150,000 segments: 565 / 467 / 486 us from the offsets, 450 / 437
     // / 452 from the ids; 2,000,000 of 256 columns in 100,000: 422 / 349 / 377 and 336 / 346 / 351.
     const int rows_log2 = seg_bwd_rows_log2(F, V);
+    // So do gradient rows (and recipients) that the MALL does not hold, whose reads the ids' would evict (us
+    // from the offsets / from the ids, fp32 rows of 256 columns: 8,000,000 in 400,000 segments, sum 1,590 /
+    // 1,860, mean 1,513 / 2,221, recorded max 1,945 / 2,129; max of 4,000,000 in 133,333 803 / 1,103, whose sum
+    // reads 136 MB and stays with the ids: 740 / 668).
     // (the kernels that read the ids move rows of any width in whole vectors, these do not)
-    const bool use_first = (size_t)nnz * is >= kBcastOffsetsMinBytes && (nnz >> rows_log2) >= num_segments &&
-                           (V == (es == 2 ? 8 : 4) || F < 4);
+    const size_t rows_read = (size_t)(num_segments * F) * (mx ? 8 : 4);
+    const bool offsets_pay = (size_t)nnz * is >= kBcastOffsetsMinBytes ||
+                             (gb >= ((size_t)64 << 20) && rows_read > kBcastOffsetsMinBytes);
+    const bool use_first = offsets_pay && (nnz >> rows_log2) >= num_segments && (V == (es == 2 ? 8 : 4) || F < 4);
     const bool from_off = mean || use_first;
     const size_t o_arg = 0,
                  arg_b = mx && !given ? align256((size_t)(num_segments * F) * (seg_bwd_arg32(nnz) ? 4 : 8)) : 0;

@@ -40,3 +40,37 @@ def test_flat_gradients(F, dtype, shift):
     wrong[0], wrong[-1] = -1, S + 3                        # out of range: zero rows
     geot.segment_reduce_backward(g, wrong, "sum", grad_src=out)
     assert torch.all(out[0] == 0) and torch.all(out[-1] == 0) and torch.equal(out[1:-1], g[i[1:-1]].to(dtype))
+
+
+@pytest.mark.parametrize("F", [31, 32, 47, 48, 100])
+@pytest.mark.parametrize("S", [60, 300])
+def test_mean_of_short_and_long_segments(F, S):
+    """The mean's two load orders (segments of 34 and of 7 rows, from 32 columns on), with ids out of range."""
+    rng = np.random.default_rng(F + S)
+    i = torch.from_numpy(np.sort(rng.integers(0, S, 2053))).to(DEV)
+    i[0], i[-1] = -1, S + 3
+    g = torch.randn(S, F, device=DEV)
+    counts = torch.bincount(i[1:-1], minlength=S).clamp_(min=1).float()
+    say(f"mean of segments F={F} S={S}")
+    got = geot.segment_reduce_backward(g, i, "mean")
+    assert torch.equal(got[1:-1], (g * (1.0 / counts)[:, None])[i[1:-1]])
+    assert torch.all(got[0] == 0) and torch.all(got[-1] == 0)
+
+
+def test_gradient_rows_beyond_the_cache():
+    """More than 200 MB of gradient rows (with their recipients) in segments of a block's rows and more, which take
+    the segments from the offsets: copies, so exact."""
+    n, S, F = 1_700_000, 104_000, 256
+    g = torch.Generator(device=DEV).manual_seed(1)
+    i = torch.sort(torch.randint(0, S, (n,), device=DEV, generator=g)).values
+    go = torch.randn(S, F, device=DEV, generator=g)
+    arg = torch.randint(0, n, (S, F), device=DEV, generator=g, dtype=torch.int32)
+    arg[i[::3]] = torch.arange(0, n, 3, device=DEV, dtype=torch.int32)[:, None]     # some recipients
+    say("gradient rows beyond the cache")
+    for idx in (i, i.int()):
+        got = geot.segment_reduce_backward_max_arg(go, idx, arg, torch.float32)
+        assert torch.equal(got, torch.where(arg[i] == torch.arange(n, device=DEV)[:, None], go[i], 0.0))
+    del got
+    big = torch.randn(2 * S, F, device=DEV, generator=g)
+    j = torch.sort(torch.randint(0, 2 * S, (2 * n,), device=DEV, generator=g)).values
+    assert torch.equal(geot.segment_reduce_backward(big, j, "sum"), big[j])

@@ -1364,7 +1364,7 @@ static geot_status_t gs_backward(const void *X, geot_dtype_t x_type, int64_t num
     const size_t o_key = transpose && !packed ? take((size_t)nnz * 8) : 0;
     const size_t o_row = transpose && !packed ? take((size_t)nnz * 8) : 0;
     const size_t o_w = transpose && !packed ? take((size_t)nnz * 4) : 0;
-    const size_t o_part = pull ? take(pull_part_bytes(nnz, F)) : 0;
+    const size_t o_part = pull ? take(pull_part_bytes(nnz, F, V)) : 0;
     // the gather over the transposed list (sum, mean): grad_X = the sum of coef * grad_out rows
     Problem tp{true, grad_out, num_rows, nullptr, nullptr, nullptr, nnz, nx, F, GEOT_OP_SUM, grad_X};
     tp.idx32 = packed ? 1 : 0;

@@ -902,13 +902,18 @@ __global__ __launch_bounds__(256) void gs_bwd_max_arg_run_kernel(const typename 
 // slot 0 for the run's first column, slot 1 for its last), which pull_join_kernel adds. Records
 // load kU at a time, grad_out rows only where the record's edge receives one of the thread's
 // features (the SpMM graph: 5.34 -> 4.53 ms; most records receive none).
-// Records per run: short ones where there are few groups, long ones where the partials of columns
-// that span runs cost more than the balance gives (whole gradient w.r.t. X, us at runs of 32 / 64 /
-// 128 / 256 / 512: 400,000 edges of 64 columns 131 / 136 / 158 / 204 / 298; 1,000,000 of 100: 295 /
-// 303 / 288 / 316 / 421; 8,000,000 of 64: 751 / 732 / 728 / 768 / 703; the SpMM graph 5,794 / 5,482
-// / 5,298 / 5,200 / 5,217). At most 256: a run is one chain of sums, and longer ones round further off.
-int pull_run(int64_t n) {
-    return n >= ((int64_t)1 << 24) ? 256 : n >= ((int64_t)1 << 20) ? 128 : 32;
+// Records per run (`tpr` threads a row): long ones cost fewer partials of columns that span runs, short ones
+// keep the chip filled, which takes more groups the fewer threads each has. Whole gradient w.r.t. X from
+// recorded recipients, us at runs of 32 / 64 / 128 / 256, 10 edges a source, uniform: 400,000 edges of 4
+// columns 84 / 107 / 156 / 235; 3,000,000 of 4 187 / 181 / 218 / 315, and 60 edges a source drawn with
+// popularity 214 / 167 / 168 / 182; 20,000,000 of 4 1,340 / 1,256 / 1,231 / 1,263; 150,000 of 256 86 / 78 / 88
+// / 130; 400,000 of 256 185 / 182 / 174 / 166; 900,000 of 256 390 / 374 / 369 / 359; the SpMM graph 5,794 / 5,482 /
+// 5,298 / 5,200. At most 256: a run is one chain of sums, and longer ones round further off.
+int pull_run(int64_t n, int tpr) {
+    const int64_t mi = (int64_t)1 << 20, lanes = n * tpr;
+    if ((n >= 16 * mi && tpr >= 8) || (lanes >= 48 * mi && tpr == 64)) return 256;
+    if (n >= 16 * mi || lanes >= 19 * mi) return 128;
+    return n >= mi || lanes >= 8 * mi ? 64 : 32;
 }
 
 template <int V, bool COOP>
@@ -2278,8 +2283,8 @@ hipError_t launch_transpose(const void *col, int64_t nx, const void *row, int id
                               arrays_written, st);
 }
 
-size_t pull_part_bytes(int64_t n, int64_t F) {
-    const int run = pull_run(n);
+size_t pull_part_bytes(int64_t n, int64_t F, int V) {
+    const int run = pull_run(n, row_threads((int)(F / V)));
     return (size_t)((n + run - 1) / run) * 2 * (size_t)F * 4;
 }
 
@@ -2288,7 +2293,7 @@ hipError_t launch_gs_bwd_x_max_pull(const int32_t *rec, const int64_t *off, cons
     if (nx <= 0 || F <= 0 || n <= 0) return hipSuccess;
     if (!(V == 1 || V == 2 || V == 4) || F % V != 0) return hipErrorInvalidValue;
     const int nvec = (int)(F / V);
-    const int run = pull_run(n);
+    const int run = pull_run(n, row_threads(nvec));
     const int64_t gp = grid_rows((n + run - 1) / run, nvec, 1), gj = (nx + 255) / 256;
     if (gp > 0x7fffffffLL || gj > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const int4 *r = reinterpret_cast<const int4 *>(rec);

@@ -188,7 +188,7 @@ size_t transpose_scratch_bytes(int64_t n, int64_t nx, bool edges);
 // fused form, max, w.r.t. X from the packed transposed list (rec, column starts off, both from
 // launch_transpose) and the 32-bit recipients arg [R x F]: grad_X written whole, no atomics. part
 // (pull_part_bytes) holds the partial sums of columns that span the pass's runs of records.
-size_t pull_part_bytes(int64_t n, int64_t F);
+size_t pull_part_bytes(int64_t n, int64_t F, int V);
 hipError_t launch_gs_bwd_x_max_pull(const int32_t *rec, const int64_t *off, const void *arg, const float *gout, int64_t n,
                                     int64_t nx, int64_t R, int64_t F, int V, float *part, float *gX, hipStream_t st);
 

@@ -75,7 +75,7 @@ def test_pull_skips_columns_out_of_range(n):
 
 def test_pull_sums_in_short_chains():
     """Columns of 512 terms of 1 + 2^-16 in a long list: runs are one chain of at most 256, which is exact, as
-    is the sum of two; past the 256th term a chain would lose the 2^-16 of every one."""
+    are the sums of those; past the 256th term a chain would lose the 2^-16 of every one."""
     n = (1 << 24) + 512
     row = torch.arange(n, device=DEV)
     col = row // 512
@@ -85,3 +85,26 @@ def test_pull_sums_in_short_chains():
     x = torch.zeros(nx, 1, device=DEV)
     gx, _ = geot.gather_scatter_backward_max_arg(x, col, None, row, g, row.int()[:, None].contiguous(), need_weight=False)
     assert torch.all(gx == 512 * (1 + 2.0 ** -16))
+
+
+@pytest.mark.parametrize("n,F", [(170_000, 256), (330_000, 256), (800_000, 256), ((1 << 20) + 77, 3)])
+def test_pull_run_lengths(n, F):
+    """Lists long and rows wide enough for runs of 64, 128 and 256 records: columns of 1 to 700 records, many
+    ending beside a run's edge. Small integers, so the sums are exact in any order."""
+    rng = np.random.default_rng(n)
+    lens = np.resize([64, 128, 256, 63, 65, 127, 129, 255, 257, 1, 700, 3, 31], n)
+    col = np.repeat(np.arange(n), lens)[:n]
+    nx = int(col[-1]) + 3
+    rng.shuffle(col)
+    R = n // 6
+    row = np.sort(rng.integers(0, R, n))
+    x = torch.randint(-20, 21, (nx, F), device=DEV).float()
+    g = torch.randint(-2, 3, (R, F), device=DEV).float()
+    c, r = up(col), up(row)
+    say(f"pull runs n={n} F={F}")
+    _, arg = geot.gather_scatter_max_arg(x, c, None, r, R)
+    gx, _ = geot.gather_scatter_backward_max_arg(x, c, None, r, g, arg, need_weight=False)
+    hit = (arg >= 0).nonzero(as_tuple=True)
+    want = torch.zeros(nx, F, device=DEV)
+    want.index_put_((c[arg[hit].long()], hit[1]), g[hit], accumulate=True)
+    assert torch.equal(gx, want)

@@ -650,10 +650,18 @@ struct EpPlan {
 
 // Joining the partials directly is one launch for the two or three of the levels (2,000,000 rows of
 // 16 columns: 36 against 43 us for the call, of 64: 100 against 109, 65,536 of 32: 12 against 15).
-// But one block reads all partials of the longest segment, at about 80 GB/s: with half (all but
-// 5 %) of the 2,000,000 rows of 64 columns in one segment 112 (118) against 107 (105) us. So it takes lists
-// up to kJoinBytes, where segments average at most kJoinSpan blocks' rows; a list twice as long
-// costs less than 4 % of its call by levels.
+// But one block reads all partials of the longest segment, at about 80 GB/s, so the line lies where inputs
+// without such a segment still gain. Us joined / by levels, by what the longest segment holds (list bytes:
+// chunks x F x 4; "law": a power law over all segments):
+//   list    rows x columns                    even      law       a tenth   half      95 %
+//   0.5 MB  1,000,000 x 64                    53 / 61   63 / 63   60 / 61   64 / 63   71 / 64
+//   1.0 MB  2,000,000 x 64                    100 / 108 111 / 111 107 / 108 113 / 107 122 / 107
+//   1.6 MB  200,000 x 256, gathered           39 / 49   47 / 51   46 / 49   58 / 50   74 / 54
+//   2.0 MB  1,000,000 x 128                   97 / 107  108 / 111 104 / 107 115 / 105 133 / 107
+//   2.3 MB  1,200,000 x 128 bf16, gathered    72 / 82   80 / 83   80 / 82   98 / 83   112 / 79
+// A segment of half of all rows or more, which the host cannot see, costs up to a fifth (of 95 %, two fifths).
+// So it takes lists up to kJoinBytes, where segments average at most kJoinSpan blocks' rows; a list twice as
+// long gains less than 4 % of its call over the levels.
 constexpr int64_t kJoinChunks = 16384, kJoinBytes = (int64_t)5 << 19, kJoinSpan = 4;
 
 geot_status_t plan_ep(const Problem &p, const Resolved &r, EpPlan *pl) {

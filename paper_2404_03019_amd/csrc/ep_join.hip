@@ -13,7 +13,8 @@
 // Bound by latency (a launch and one or two trips to memory), as the partial levels are, but it is
 // one launch where they are two or three: 3,908 partials of 16 columns 4.0 us against 7.4 + 3.9,
 // 4,688 of 128 columns 4.9 against 6.9 + 4.8 + 4.5. The levels keep the inputs with many partials, or with
-// segments that cross many blocks each, which they reduce in logarithmic depth.
+// segments that cross many blocks each, which they reduce in logarithmic depth. One segment of half of all
+// rows is read by one block here, which makes the call 1 to 20 % slower than by levels.
 #include <type_traits>
 
 #include "common.h"

@@ -27,23 +27,28 @@
  *  - `out` is overwritten in full, including empty segments (it is never
  *    accumulated into). Empty segments hold GEOT_EMPTY_FILL for every op.
  *  - Temporary device memory (partial results of segments that cross block
- *    boundaries) comes from a stream-ordered pool owned by the library; the
- *    reductions keep one buffer per (device, stream) for reuse (see
- *    geot_release_scratch). Any thread may call the library, but calls that
- *    share one stream must be issued one after the other: two host threads
- *    enqueuing on the same stream at once would interleave their kernels
- *    over that stream's buffer. Different streams are independent. The *_ws
- *    forms take this memory from the caller instead and allocate nothing.
- *  - The reduction calls (forward) can be captured in a HIP graph and replayed:
- *    they keep no per-call host state and issue no memset. Make one call of the
+ *    boundaries, the gradients' tables) comes from a stream-ordered pool owned
+ *    by the library, which keeps one buffer per (device, stream) for reuse (see
+ *    geot_release_scratch). Any thread may call the library, also on a stream
+ *    that other threads use: a call holds the stream's buffer until its last
+ *    kernel on it is enqueued, so the kernels of calls that share a stream
+ *    never mix on the buffer. Different streams are independent. The *_ws
+ *    forms take this memory from the caller instead and allocate nothing; a
+ *    workspace belongs to one call at a time.
+ *  - The reduction calls (forward) and the segment gradients can be captured in
+ *    a HIP graph and replayed: they keep no per-call host state and issue no memset. Make one call of the
  *    same shapes on the capture stream first, so the stream's buffer exists
  *    before the capture; a captured call that would need a larger buffer
  *    returns GEOT_ERROR_INVALID_VALUE instead of allocating. A buffer that a
  *    graph captured is never freed when a later call outgrows it (it is kept
  *    for the graph until geot_release_scratch, which invalidates such graphs).
- *    The gradient calls and geot_transpose_edges take their temporaries from
- *    the pool on every call (stream-ordered allocations, recorded as graph
- *    allocations under capture).
+ *    The fused-form gradients can be captured too: their temporaries then come
+ *    from the pool (stream-ordered allocations, recorded as graph allocations),
+ *    as they do outside a capture above 64 MB a call; up to that they live in
+ *    the stream's buffer. The reductions inside them (and mean's row starts)
+ *    use the stream's buffer in every case, so the rule of a call made before
+ *    the capture holds for them as well. geot_transpose_edges takes its
+ *    temporaries from the pool on every call.
  *  - Preconditions: the index is non-decreasing and 0 <= index < num_segments;
  *    for the gather form 0 <= col < num_x_rows. They are not checked by the
  *    reduction calls (geot_check_index checks them). Violations give
@@ -112,9 +117,10 @@ typedef struct {
     int32_t family; /* geot_family_t */
     int32_t vec;    /* elements per lane load: 1, 2, 4, or 8 for 16-bit storage (the typed calls), or 3 for
                        fp32 rows of 3 floats; clamped down to what F and alignment allow. With vec 8,
-                       lanes is at most 32. fp32 rows whose width is no multiple of 4 may still take
-                       vec 4: the vector that would cross a row's end reads the row's last 4
-                       floats instead, overlapping its neighbour */
+                       lanes is at most 32. Rows whose width is no multiple of vec may still take
+                       it (4 for fp32; 8, 4 or 2 for 16-bit storage, at any 2-byte address): the
+                       vector that would cross a row's end reads the row's last vec elements
+                       instead, overlapping its neighbour */
     int32_t lanes;  /* lanes sharing one row: 1, 2, 4, 8, 16, 32 or 64 */
     int32_t rows;   /* EP: consecutive rows per row group (1..4096) */
     int32_t groups; /* SP: row groups of one wave that cooperate on one segment (1..64/lanes) */
@@ -339,7 +345,9 @@ geot_status_t geot_segment_reduce_backward_typed(const float *grad_out, const vo
  * num_rows * F edge numbers (4 bytes each below 2^32 - 1 edges, else 8; the
  * same pool); below 2^32 - 1 edges and 2^31 X rows each row of grad_X then
  * sums the terms of its column's records whose edge is the recipient (the same
- * transposed list), else the recipients' terms are added atomically, in
+ * transposed list, in runs of 32 to 256 records, the more the larger the call;
+ * columns that span runs take two rows of F floats per run: 2 * 4 * F / 32
+ * bytes an edge at the most), else the recipients' terms are added atomically, in
  * arrival order, so a column that receives very many terms of one sign may
  * exceed the fp32 bound given below. Mean takes (num_rows + 1) int64 row
  * starts.
@@ -488,10 +496,11 @@ geot_status_t geot_index_stats(const int64_t *sorted_index, int64_t nnz, int64_t
 geot_status_t geot_check_index(const int64_t *sorted_index, int64_t nnz, int64_t num_segments,
                                const int64_t *col, int64_t num_x_rows, void *stream);
 
-/* Reduction calls keep one temporary device buffer per (device, stream), reused
- * in stream order and grown on demand (partials of block-crossing segments:
- * two rows of F floats per block, about 1.5 % of the input for F = 128; or
- * num_segments + 1 segment starts). This frees every such buffer after
+/* The library keeps one temporary device buffer per (device, stream), reused
+ * in stream order and grown on demand, by half at least (partials of
+ * block-crossing segments: two rows of F floats per block, about 1.5 % of the
+ * input for F = 128; or num_segments + 1 segment starts; the segment gradients'
+ * tables; up to 64 MB of a fused gradient's). This frees every such buffer,
  * synchronizing its stream, and the buffers that captured graphs held (those
  * graphs must not be replayed afterwards); later calls allocate again. Call it
  * before destroying a stream the library was used on, or to return the memory. */

@@ -219,6 +219,23 @@ geot_status_t stream_scratch(size_t bytes, hipStream_t st, void **user, GapList 
     return GEOT_SUCCESS;
 }
 
+// Whether a call on `st` gets `bytes` of its buffer: outside a capture always, in one without growing it.
+bool scratch_holds(size_t bytes, hipStream_t st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = 0;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || hipGetDevice(&dev) != hipSuccess) return false;
+    if (cap == hipStreamCaptureStatusNone) return true;
+    std::shared_ptr<StreamCtx> ctx;
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        const auto it = g_cache.find(StreamKey{dev, st});
+        if (it == g_cache.end()) return false;
+        ctx = it->second;
+    }
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    return !ctx->gone && ctx->bytes >= kGapArea + ((bytes + 255) & ~(size_t)255);
+}
+
 // Device memory of one reduction call given by the caller (the *_ws calls): its first
 // kGapArea bytes hold the gap list, zeroed by the call itself, then the partials.
 struct Workspace {
@@ -1160,18 +1177,20 @@ static geot_status_t seg_backward(const float *grad_out, const void *sorted_inde
     // reads 136 MB and stays with the ids: 740 / 668).
     // (the kernels that read the ids move rows of any width in whole vectors, these do not)
     const size_t rows_read = (size_t)(num_segments * F) * (mx ? 8 : 4);
-    const bool offsets_pay = (size_t)nnz * is >= kBcastOffsetsMinBytes ||
-                             (gb >= ((size_t)64 << 20) && rows_read > kBcastOffsetsMinBytes);
-    const bool use_first = offsets_pay && (nnz >> rows_log2) >= num_segments && (V == (es == 2 ? 8 : 4) || F < 4);
-    const bool from_off = mean || use_first;
+    const bool many_ids = (size_t)nnz * is >= kBcastOffsetsMinBytes;
+    const bool offsets_pay = many_ids || (gb >= ((size_t)64 << 20) && rows_read > kBcastOffsetsMinBytes);
+    bool use_first = offsets_pay && (nnz >> rows_log2) >= num_segments && (V == (es == 2 ? 8 : 4) || F < 4);
     const size_t o_arg = 0,
                  arg_b = mx && !given ? align256((size_t)(num_segments * F) * (seg_bwd_arg32(nnz) ? 4 : 8)) : 0;
-    const size_t o_off = o_arg + arg_b, o_first = o_off + (from_off ? align256((size_t)(num_segments + 1) * 8) : 0);
+    const size_t o_off = o_arg + arg_b, o_first = o_off + align256((size_t)(num_segments + 1) * 8);
     const int64_t blocks = seg_bwd_blocks(nnz, F, V);
+    // (up to 200 MB of ids a captured call whose stream's buffer is too small for this reads the ids)
+    if (use_first && !many_ids && !scratch_holds(o_first + (size_t)blocks * 16, st)) use_first = false;
+    const bool from_off = mean || use_first;
     GapList gaps;
     if ((mx && !given) || from_off) {
-        geot_status_t s = stream_scratch(o_first + (use_first ? (size_t)blocks * 16 : 0), st, &scratch,
-                                         from_off ? &gaps : nullptr, &held);
+        geot_status_t s = stream_scratch(use_first ? o_first + (size_t)blocks * 16 : from_off ? o_first : arg_b, st,
+                                         &scratch, from_off ? &gaps : nullptr, &held);
         if (s != GEOT_SUCCESS) return s;
     }
     void *arg = mx ? (given ? (void *)given : scratch) : nullptr;

@@ -74,3 +74,36 @@ def test_gradient_rows_beyond_the_cache():
     big = torch.randn(2 * S, F, device=DEV, generator=g)
     j = torch.sort(torch.randint(0, 2 * S, (2 * n,), device=DEV, generator=g)).values
     assert torch.equal(geot.segment_reduce_backward(big, j, "sum"), big[j])
+
+
+@pytest.mark.parametrize("op", ["sum", "max"])
+def test_gradient_rows_beyond_the_cache_captured_first(op):
+    """Captured on a stream that no call has run on: the ids' path, which takes no temporary memory."""
+    n, S, F = 1_700_000 * (2 if op == "sum" else 1), 104_000 * (2 if op == "sum" else 1), 256
+    g = torch.Generator(device=DEV).manual_seed(2)
+    i = torch.sort(torch.randint(0, S, (n,), device=DEV, generator=g)).values
+    go = torch.randn(S, F, device=DEV, generator=g)
+    arg = torch.zeros(S, F, device=DEV, dtype=torch.int32)
+    first = torch.searchsorted(i, torch.arange(S, device=DEV))
+    arg[:] = first[:, None].int()
+    out = torch.empty(n, F, device=DEV)
+
+    def call():
+        if op == "sum":
+            geot.segment_reduce_backward(go, i, "sum", grad_src=out)
+        else:
+            out.copy_(geot.segment_reduce_backward_max_arg(go, i, arg, torch.float32))
+
+    say(f"capture without a call before it, {op}")
+    torch.cuda.synchronize()
+    geot.release_scratch()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    for _ in range(3):
+        go.mul_(0.5)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = go[i] if op == "sum" else torch.where((first[i] == torch.arange(n, device=DEV))[:, None], go[i], 0.0)
+        assert torch.equal(out, want)

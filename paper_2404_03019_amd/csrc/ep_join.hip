@@ -146,8 +146,9 @@ __global__ __launch_bounds__(kJoinBlock) void ep_join_kernel(const EpArgs a, con
     }
     __syncthreads();
     // this thread's share of the run that starts at block `cl`: the lo partials of blocks k0, k0 + by,
-    // ... (kU at a time, at most `trips` times); returns whether the run may go on behind them. Each turn's
-    // partials are combined by themselves first: no chain of sums is longer than a turn's or the turns
+    // ... (kU at a time, at most `trips` times); returns whether the run may go on behind them. A turn's sums
+    // are added up by themselves first: no chain of them is longer than a turn's or the turns (maxima join
+    // the total directly: 386,951 rows of 8 columns, Zipf lengths, 14.8 us by turns, 14.4 so)
     auto walk = [&](auto ut, int32_t seg, int64_t k0, int64_t by, int trips, int j, bool lane, float *v, uint32_t *vi, int64_t &n) {
         constexpr int kU = decltype(ut)::value;
         bool more = true;
@@ -162,18 +163,17 @@ __global__ __launch_bounds__(kJoinBlock) void ep_join_kernel(const EpArgs a, con
                 cnt[u] = k < chunks ? count_of(2 * kk) : 0;
                 load(2 * kk, j, lane, x[u], xi[u]);
             }
-            more = cnt[0] > 0 && id[0] == seg;
-            if (!more) break;
-            n += cnt[0];
+            const bool any = cnt[0] > 0 && id[0] == seg;
 #pragma unroll
-            for (int u = 1; u < kU; ++u) {   // the run is contiguous: past its end nothing matches
+            for (int u = 0; u < kU; ++u) {   // the run is contiguous: past its end nothing matches
                 more = more && cnt[u] > 0 && id[u] == seg;
                 if (more) {
-                    take(x[0], xi[0], x[u], xi[u]);
+                    if constexpr (RED != RED_SUM) take(v, vi, x[u], xi[u]);
+                    else if (u > 0) take(x[0], xi[0], x[u], xi[u]);
                     n += cnt[u];
                 }
             }
-            take(v, vi, x[0], xi[0]);
+            if (RED == RED_SUM && any) take(v, vi, x[0], xi[0]);
         }
         return more && k0 < chunks;
     };
